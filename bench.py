@@ -36,8 +36,8 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "fill_kernel_fcc1M_traffic.md")
 # sources the fill kernel is compiled from: a recorded traffic figure is
 # reported only while they are unchanged
-FILL_SOURCES = ["paper_1906_06317_amd/csrc/pairs.hip", "paper_1906_06317_amd/csrc/pair_common.hpp",
-                "paper_1906_06317_amd/csrc/internal.hpp"]
+FILL_SOURCES = ["paper_1906_06317_amd/csrc/" + f
+                for f in ("fill_kernel.hpp", "pair_list.hpp", "pair_common.hpp", "internal.hpp")]
 
 
 def parse():

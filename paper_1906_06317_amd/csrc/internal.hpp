@@ -65,7 +65,7 @@ struct CellList {
 
 struct Workspace {
     unsigned* status;             // device status bits
-    unsigned long long* counters; // [24] general counters (k-NN deferred count, batch queues)
+    unsigned long long* counters; // [24] general counters (k-NN deferred count)
     CellList pts;
     CellList qry;                 // == pts for self queries
     // canonical-row mode: int64 exclusive scan of row counts
@@ -140,6 +140,7 @@ void launch_build_cells_batch(const float* pts, CellList& cl, const FrameInfo* f
                               int* part, bool global_frames, unsigned* status, hipStream_t s);
 bool expanded_test_ok(const BoxPrep& bp, const Grid& g, double r);
 int check_cutoff(const BoxPrep& bp, double r);
+int pair_split(long long ncells, long long nq);
 
 // Geometry of a pair query (pairs.hip).
 struct PairGeom {
@@ -178,14 +179,21 @@ struct BatchGeom {
     int nframes;
     int ncells;        // all frames
     float r2max;
-    int run;           // home cells per work-queue item
-    unsigned long long* queue;  // [16] zeroed counters: 8 per-XCD queues per pass
+    int run;           // work items per queue draw, at most
+    int split;         // wavefronts sharing a home cell's queries (1: a work item is a cell)
+    unsigned long long* queue;  // zeroed: 8 per-XCD counters per pass, kQueueStride apart
 };
+constexpr int kQueueStride = 16;  // in 64-bit words: every counter on its own 128-byte line
+constexpr size_t kQueueBytes = 16 * kQueueStride * sizeof(unsigned long long);
 // waves: wavefronts per workgroup (2 or 4)
 void launch_count_batch(const PairArgs& a, const BatchGeom& b, int dim, int excl, int blocks_cap,
                         int waves, hipStream_t s);
 void launch_fill_batch(const PairArgs& a, const BatchGeom& b, int dim, int excl, int blocks_cap,
                        int waves, hipStream_t s);
+void launch_fill_batch_2d(const PairArgs& a, const BatchGeom& b, int excl, int blocks_cap,
+                          int waves, hipStream_t s);
+void launch_fill_batch_3d(const PairArgs& a, const BatchGeom& b, int excl, int blocks_cap,
+                          int waves, hipStream_t s);
 
 // excl: 0 keep i == j, 1 points query themselves (drop the query's own
 // entry), 2 separate query points (drop j == i by index).
@@ -195,6 +203,8 @@ int device_cus();
 
 void launch_count(const PairArgs& a, int dim, int excl, hipStream_t s);
 void launch_fill(const PairArgs& a, int dim, int excl, bool nl, bool hist, hipStream_t s);
+void launch_fill_2d(const PairArgs& a, int excl, bool nl, bool hist, hipStream_t s);
+void launch_fill_3d(const PairArgs& a, int excl, bool nl, bool hist, hipStream_t s);
 // Orders every complete row of a CSR list by neighbour index (distances follow).
 void launch_sort_rows(const int64_t* offsets, int64_t nq, int32_t* idx, float* dist,
                       int64_t capacity, hipStream_t s);

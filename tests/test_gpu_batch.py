@@ -289,3 +289,27 @@ def test_capacity_retry_and_block_shapes(ppa):
         assert cfg["cells_per_item"] >= 1 and cfg["waves_per_workgroup"] in (2, 4)
         shapes.add((cfg["cells_per_item"], cfg["waves_per_workgroup"]))
     assert len(shapes) >= 3
+
+
+@pytest.mark.parametrize("count,n_lo,n_hi", [(1, 1500, 1500), (64, 1100, 1300), (65, 1100, 4000),
+                                              (131, 1100, 1500), (3, 60000, 60001)])
+def test_queue_runs_parts_and_frame_search(ppa, count, n_lo, n_hi):
+    """Cells shared by several wavefronts, the runs' taper at small and large
+    totals, and the 64-way frame search around 64 and 128 frames: histograms
+    and lists equal those of one call per frame."""
+    import torch
+    frames = _frames(500 + count, count, n_lo, n_hi)
+    plan, pts = _plan(ppa, frames)
+    hist, nl = plan.run(pts)
+    first = 0
+    for f, s in enumerate(frames):
+        box = ppa.Box(s.L, s.tilt, s.dim)
+        c, one = ppa.rdf_counts(box, s.points, BINS, R_MAX, neighbor_list=True)
+        a, b = int(plan.offsets_host[f]), int(plan.offsets_host[f + 1])
+        assert torch.equal(hist[f], c), f
+        assert torch.equal(nl.counts[a:b], one.counts), f
+        last = first + one.n_pairs
+        assert torch.equal(nl.point_idx[first:last], one.point_idx), f
+        assert torch.equal(nl.dist[first:last], one.dist), f
+        first = last
+    assert first == nl.n_pairs
