@@ -7,10 +7,11 @@
 //
 // Union-find over the labels array as the parent forest.  A seed pass
 // points every point at its smallest listed neighbour; hooking rounds over
-// all bonds (the larger label pointed at the smaller by atomic minimum, a
-// step of the Shiloach-Vishkin kind) alternate with passes that point every
-// node at its root, until a round changes nothing, so the large components
-// form flat; a last lock-free union pass over every bond makes the result
+// the bonds (the root of a point's component pointed at the smallest label
+// among the point's neighbours, by plain stores of which any may win)
+// alternate with passes that point every node at its root, until a round
+// changes nothing, so the
+// large components form flat; a last lock-free union pass over every bond makes the result
 // exact, most of its unions ending after two one-step finds.  Finds in the union passes halve paths with plain stores; the
 // compress passes only read the forest and write their own entries.  A union finds
 // both roots and links the larger under the smaller with a compare-and-swap
@@ -21,8 +22,11 @@
 // shrinks on every retry, so every union ends.  A compress pass sets every
 // label to its root, each lane writing only its own entry (by atomic
 // minimum, which keeps a root a concurrent union may have written); the
-// compact numbering is a scan over the roots.  For a list the caller declares
-// symmetric, the rounds sample two bonds per row and the union pass skips the
+// compact numbering is a scan over the roots.  What bounds it: reads of
+// labels at random places and, where a pass needs them, atomics (to one
+// address about 12 ns each, serialised across the XCDs; to scattered ones
+// about 5 per ns).  For a list the caller declares
+// symmetric, later rounds sample two bonds per row and the union pass skips the
 // points of the largest sampled component (their bonds to other points are
 // in those points' rows).
 #include "internal.hpp"
@@ -33,11 +37,23 @@ namespace {
 
 constexpr int kClBlock = 256;
 constexpr int kClRounds = kClusterRounds;  // hooking rounds at most
-constexpr int kClSampled = 2;              // bonds per row the rounds hook (symmetric lists)
+constexpr int kClFirst = 4;                // bonds per row of the first round (symmetric lists)
+constexpr int kClSampled = 2;              // and of the later ones
 
 __device__ __forceinline__ int parent_of(int* p, int x)
 {
     return __hip_atomic_load(&p[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A label read through the caches, and a parent written through them (the
+// hooking rounds: racing lanes, no ordering needed; a word is never torn).
+__device__ __forceinline__ int parent_cached(int* p, int x)
+{
+    return __hip_atomic_load(&p[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ void set_parent(int* p, int x, int v)
+{
+    __hip_atomic_store(&p[x], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 // Root of x, without writes: the lanes of a large component all walk
@@ -110,6 +126,15 @@ __device__ __forceinline__ bool row_bounds(const int64_t* offsets, int i, long l
     return true;
 }
 
+// Four consecutive neighbours of a row from bond e (the last one repeated
+// past the row's end), read together so that their latencies overlap.
+__device__ __forceinline__ void four_bonds(const int32_t* __restrict__ idx, long long e,
+                                           long long e1, int (&j)[4])
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) j[k] = idx[e + k < e1 ? e + k : e1 - 1];
+}
+
 // First links: every point to the smallest of itself and its listed
 // neighbours (each lane writes only its own parent, a smaller index, so the
 // result is a valid forest of unions without any atomics).
@@ -123,22 +148,33 @@ __global__ void __launch_bounds__(kClBlock) cl_seed_kernel(const int64_t* __rest
     long long e0, e1;
     row_bounds(offsets, i, capacity, status, e0, e1);
     int m = i;
-    for (long long e = e0; e < e1; ++e) {
-        const int j = idx[e];
-        if (j < 0 || j >= n) {
-            atomicOr(status, kStatusBadList);
-            continue;
+    for (long long e = e0; e < e1; e += 4) {
+        int j[4];
+        four_bonds(idx, e, e1, j);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (j[k] < 0 || j[k] >= n) {
+                atomicOr(status, kStatusBadList);
+                continue;
+            }
+            m = j[k] < m ? j[k] : m;
         }
-        m = j < m ? j : m;
     }
     labels[i] = m;
 }
 
-// One hooking round over every bond: the larger of the two current labels
-// is pointed (atomic minimum) at the smaller.  A hook may replace an earlier
-// parent, dropping that link, but it only ever joins bonded points and keeps
-// every parent below its node, so the forest stays a valid subset of the
-// components; the closing union pass restores anything dropped.
+// One hooking round over every bond (first > 0: the first `first` bonds of a
+// row): the root of point i is pointed at the smallest label among i's
+// neighbours; with BOTH (a list that may hold a bond in one row only) the
+// root of a neighbour with a larger label is also pointed at i's.  Labels
+// are flat here (every label is a root).  A hook is a plain store: of
+// several hooks of one root any may win, and each joins bonded points and
+// keeps the parent below its node, so the forest stays a valid subset of the
+// components, and every root that has a smaller neighbour is hooked; later
+// rounds and the closing union pass join what was left.  Atomic minima
+// instead cost 165 us a round (2^20 points, about 5 per ns across the XCDs),
+// and only choose which smaller neighbour a root hangs under.
+template <bool BOTH>
 __global__ void __launch_bounds__(kClBlock) cl_sv_kernel(const int64_t* __restrict__ offsets,
                                                          const int32_t* __restrict__ idx, int n,
                                                          long long capacity, int first,
@@ -156,22 +192,31 @@ __global__ void __launch_bounds__(kClBlock) cl_sv_kernel(const int64_t* __restri
     if (first > 0 && e1 > e0 + first) e1 = e0 + first;  // a sample of the bonds
     // cached loads: a stale label is an older ancestor, which only makes a
     // hook weaker; the closing union pass is exact either way
-    const int li = labels[i];
+    const int li = parent_cached(labels, i);
+    int m = li;
     bool moved = false;
-    for (long long e = e0; e < e1; ++e) {
-        const int j = idx[e];
-        if (j < 0 || j >= n || j == i) continue;
-        const int lj = labels[j];
-        if (lj == li) continue;
-        const int hi = lj < li ? li : lj, lo = lj < li ? lj : li;
-        // read first: in a large component the target is one shared root
-        if (labels[hi] > lo) {
-            atomicMin(&labels[hi], lo);
-            moved = true;
+    for (long long e = e0; e < e1; e += 4) {
+        int j[4], l[4];
+        four_bonds(idx, e, e1, j);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) l[k] = j[k] < 0 || j[k] >= n ? li : parent_cached(labels, j[k]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            m = l[k] < m ? l[k] : m;
+            if (BOTH && l[k] > li && parent_cached(labels, l[k]) > li) {
+                set_parent(labels, l[k], li);
+                moved = true;
+            }
         }
     }
-    if (__ballot(moved) && (threadIdx.x & (warpSize - 1)) == __ffsll((long long)__ballot(moved)) - 1)
-        atomicOr(changed, 1);
+    // read first: in a large component the target is one shared root
+    if (m < li && parent_cached(labels, li) > m) {
+        set_parent(labels, li, m);
+        moved = true;
+    }
+    const unsigned long long any = __ballot(moved);
+    if (any && (threadIdx.x & (warpSize - 1)) == __ffsll((long long)any) - 1)
+        __hip_atomic_store(changed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Unites point i with the neighbour at position `pos` of its row (pos >= 0:
@@ -203,22 +248,43 @@ __global__ void __launch_bounds__(kClBlock) cl_hook_kernel(const int64_t* __rest
 }
 
 // The root most of kClSamples evenly spaced points share (ties: the smaller
-// root), after a compress pass: one workgroup, the samples in LDS, each
-// thread counting the samples equal to its own.
+// root), after a compress pass: one workgroup, the samples counted by root
+// in an LDS table (kClSamples roots fit; a sample whose probe sequence is
+// full is left out, which only makes the choice less representative).
 constexpr int kClSamples = 1024;
+constexpr int kClTable = 2048;
+constexpr int kClProbes = 16;
 
 __global__ void __launch_bounds__(kClSamples) cl_giant_kernel(int n, const int* labels, int* giant)
 {
-    __shared__ int s_lab[kClSamples];
+    __shared__ int s_root[kClTable], s_count[kClTable];
     __shared__ unsigned long long s_best[kClSamples / 64];
     const int t = threadIdx.x;
-    const int lab = labels[(int)(((long long)t * n) / kClSamples)];
-    s_lab[t] = lab;
+    for (int k = t; k < kClTable; k += kClSamples) {
+        s_root[k] = -1;
+        s_count[k] = 0;
+    }
     __syncthreads();
-    int c = 0;
-    for (int u = 0; u < kClSamples; ++u) c += s_lab[u] == lab ? 1 : 0;
-    // largest count first, then smallest root: one 64-bit key per thread
-    unsigned long long key = ((unsigned long long)(unsigned)c << 32) | (unsigned)(0x7fffffff - lab);
+    const int lab = labels[(int)(((long long)t * n) / kClSamples)];
+    unsigned h = (unsigned)lab * 2654435761u >> 21;  // 11 bits: kClTable slots
+    static_assert(kClTable == 1 << 11, "the hash above gives 11 bits");
+    for (int p = 0; p < kClProbes; ++p) {
+        const int old = atomicCAS(&s_root[h], -1, lab);
+        if (old == -1 || old == lab) {
+            atomicAdd(&s_count[h], 1);
+            break;
+        }
+        h = (h + 1) & (kClTable - 1);
+    }
+    __syncthreads();
+    // largest count first, then smallest root: one 64-bit key per slot
+    unsigned long long key = 0;
+    for (int k = t; k < kClTable; k += kClSamples)
+        if (s_root[k] >= 0) {
+            const unsigned long long o = ((unsigned long long)(unsigned)s_count[k] << 32) |
+                                         (unsigned)(0x7fffffff - s_root[k]);
+            key = o > key ? o : key;
+        }
     for (int sh = 32; sh > 0; sh >>= 1) {
         const unsigned long long o = __shfl_xor(key, sh);
         key = o > key ? o : key;
@@ -337,16 +403,26 @@ void launch_cluster(const ClusterArgs& a, hipStream_t s)
     // threshold of random geometric graphs) form no large component: the
     // union pass alone is faster there
     // With a symmetric list (every bond in both rows) the rounds hook only
-    // the first kClSampled bonds of each row; the root most sampled points
-    // share then marks the largest component, whose points the union pass
-    // skips (the sampling of the Afforest method).  On the 2^20-point
-    // uniform system: r = 1.2 1.73 -> 1.32 ms, r = 1.6 2.49 -> 1.28 ms.
+    // the first bonds of each row; the root most sampled points share then
+    // marks the largest component, whose points the union pass skips (the
+    // sampling of the Afforest method).  2^20-point uniform system, r = 1.2
+    // (7.2 bonds a point): 1164 us with rounds of one atomic minimum per
+    // bond, 309 us now; r = 0.95, at percolation: 1294 and 370 us, but four
+    // rounds instead of six leave the union pass 2856 us there.
     const int rounds = a.capacity < 3 * (long long)n ? 0 : kClRounds;
-    const int first = a.symmetric ? kClSampled : 0;
     for (int r = 0; r < rounds; ++r) {
         const int* prev = r > 0 ? a.round_flags + (r - 1) : nullptr;
-        hipLaunchKernelGGL(cl_sv_kernel, dim3(nb), dim3(kClBlock), 0, s, a.offsets, a.idx, n,
-                           a.capacity, first, a.labels, prev, a.round_flags + r);
+        // the first round sees small components (a seed tree holds about a
+        // row's points) and takes four bonds per row; after it a component is
+        // large enough that two reach its neighbours (every bond in the first
+        // round: 333 us instead of 309 below)
+        const int first = a.symmetric ? (r == 0 ? kClFirst : kClSampled) : 0;
+        if (a.symmetric)
+            hipLaunchKernelGGL(cl_sv_kernel<false>, dim3(nb), dim3(kClBlock), 0, s, a.offsets,
+                               a.idx, n, a.capacity, first, a.labels, prev, a.round_flags + r);
+        else
+            hipLaunchKernelGGL(cl_sv_kernel<true>, dim3(nb), dim3(kClBlock), 0, s, a.offsets,
+                               a.idx, n, a.capacity, first, a.labels, prev, a.round_flags + r);
         hipLaunchKernelGGL(cl_compress_kernel, dim3(nb), dim3(kClBlock), 0, s, n, a.labels,
                            nullptr, a.round_flags + r);
     }

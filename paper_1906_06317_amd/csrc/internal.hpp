@@ -357,7 +357,7 @@ void launch_steinhardt_setup(int l, bool want_w, double* table, unsigned* status
 void launch_steinhardt(const SteinArgs& a, hipStream_t s);
 
 // Clusters: connected components of NeighborList bonds (cluster.hip).
-constexpr int kClusterRounds = 12;  // hooking rounds at most (flags in the header)
+constexpr int kClusterRounds = 6;  // hooking rounds at most (flags in the header)
 
 struct ClusterArgs {
     const int64_t* offsets;   // [n + 1]

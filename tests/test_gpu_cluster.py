@@ -194,3 +194,36 @@ def test_symmetric_flag_small_and_bad_lists(ppa):
     idx = np.concatenate([np.array(r, np.int32) for r in rows])
     k = _compare_symmetric(ppa, n, off, idx)
     assert k == 2
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 1025, 40000])
+@pytest.mark.parametrize("symmetric", [True, False])
+def test_row_lengths_around_the_read_width(ppa, n, symmetric):
+    """Rows of 0 to 9 bonds (read four at a time; the sampled rounds take four
+    and two), point counts around the workgroup, both list kinds, with a
+    component that most points join and small ones beside it."""
+    rng = np.random.default_rng(700 + n)
+    rows = [[] for _ in range(n)]
+    group = rng.integers(0, 10, size=n)  # points of group 0..6 may bond, 7..9 stay in pairs
+    big = np.flatnonzero(group < 7)
+    for i in range(n):
+        if n < 2:
+            break
+        if group[i] < 7 and big.size > 1:
+            for j in rng.choice(big, size=int(rng.integers(0, 5))):
+                rows[i].append(int(j))
+        elif i + 1 < n and group[i] == 9:
+            rows[i].append(i + 1)
+    if symmetric:
+        for i in range(n):
+            for j in list(rows[i]):
+                if i not in rows[j]:
+                    rows[j].append(i)
+    off = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+    idx = np.array([j for r in rows for j in r], dtype=np.int32)
+    labels, cidx, sizes, k = ppa.clusters((off, idx), n, symmetric=symmetric)
+    ol, oc, os_ = oracle.clusters(n, off, idx)
+    np.testing.assert_array_equal(labels.cpu().numpy(), ol)
+    np.testing.assert_array_equal(cidx.cpu().numpy(), oc)
+    np.testing.assert_array_equal(sizes.cpu().numpy(), os_)
+    assert k == os_.shape[0]
