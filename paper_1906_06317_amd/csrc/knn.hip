@@ -116,6 +116,79 @@ __device__ __forceinline__ int count_below(const float (&d2)[NS], float T)
 // Outcome of the common path for one query.
 enum { kRowFull = 0, kRowShort = 1, kRowDefer = 2 };
 
+// Threshold T (from a first guess, at most thi) with k <= #{d^2 < T} <= 64,
+// or thi when every candidate under it is needed; blk: the searched block
+// (not r_guard or half the box) sets thi, so points beyond it may matter.
+template <int DIM, int NS>
+__device__ __forceinline__ int find_threshold(const KnnGeom& K, const float (&d2)[NS], float thi,
+                                              int blk, float& T, int& cnt)
+{
+    float lo = 0.f, hi = thi;
+    bool hi_set = false;
+    for (int it = 0; it < kKnnIter; ++it) {
+        cnt = count_below<DIM, NS>(d2, T);
+        if (cnt >= K.k && cnt <= kWave) return kRowFull;
+        if (cnt < K.k) {
+            if (T >= thi) return blk ? kRowDefer : kRowShort;
+            lo = T;
+            T = hi_set ? 0.5f * (T + hi) : fminf(fmaxf(T * 1.5f, 1e-3f * K.t0), thi);
+        } else {
+            hi = T;
+            hi_set = true;
+            T = 0.5f * (lo + T);
+        }
+    }
+    return kRowDefer;
+}
+
+// Compacts the cnt candidates under T, ranks them and writes the first `len`
+// (k, or all of a short row) to the query's row; returns this lane's rank and
+// its key in `mine` (lanes below cnt).
+template <int DIM, int NS>
+__device__ __forceinline__ int emit_row(const KnnArgs& a, unsigned long long* key,
+                                        const float (&d2)[NS], const int (&id)[NS], float T,
+                                        int state, int cnt, int qid, int lane,
+                                        unsigned long long& mine, int& len)
+{
+    const int k = a.knn.k;
+    // the rest of the buffer holds keys that sort last
+    key[lane] = kNoKey;
+    int nb = 0;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const bool h = d2[s] < T;
+        const unsigned long long m = __ballot(h);
+        if (h) key[nb + (int)lane_prefix(m)] = knn_key(d2[s], id[s]);
+        nb += __popcll(m);
+    }
+    wave_sync();
+    // Each key is ranked by one lane of every group of gsz >= cnt
+    // lanes; the groups split the buffer between them (four keys per
+    // step, independent LDS reads) and their partial ranks are summed
+    // across groups.  Past cnt the buffer holds keys that sort last.
+    const int gsz = cnt <= 16 ? 16 : (cnt <= 32 ? 32 : kWave);
+    const int ng = kWave / gsz;
+    const int share = ((cnt + ng - 1) / ng + 3) & ~3;
+    mine = key[lane & (gsz - 1)];
+    const unsigned long long* part = &key[(lane / gsz) * share];
+    int r = 0;
+    for (int u = 0; u < share; u += 4) {
+        const ulonglong2 a2 = *reinterpret_cast<const ulonglong2*>(&part[u]);
+        const ulonglong2 b2 = *reinterpret_cast<const ulonglong2*>(&part[u + 2]);
+        r += (a2.x < mine ? 1 : 0) + (a2.y < mine ? 1 : 0) + (b2.x < mine ? 1 : 0) +
+             (b2.y < mine ? 1 : 0);
+    }
+    if (gsz <= 32) r = pair_sum32(r);
+    if (gsz <= 16) r = pair_sum16(r);
+    len = state == kRowFull ? k : cnt;
+    if (lane < cnt && r < len) {
+        const long long o = (long long)k * qid + r;
+        a.out_idx[o] = (int)(unsigned)mine;
+        if (a.out_dist) a.out_dist[o] = fast_sqrt(key_d2(mine));
+    }
+    return r;
+}
+
 template <int DIM, int NS>
 __device__ __forceinline__ void knn_tile(const KnnArgs& a, const PairIn& in, const StencilLds& S,
                                          const float4* off, KnnLds& W, int C, int q0, int q1,
@@ -148,70 +221,16 @@ __device__ __forceinline__ void knn_tile(const KnnArgs& a, const PairIn& in, con
                 d2[s] = dist2<DIM>(c.x[s] - qx, c.y[s] - qy, c.z[s] - qz);
                 if (K.excl && c.id[s] == qid) d2[s] = kFar;
             }
-            // threshold with k <= count <= 64 (or every candidate under thi)
             float T = fminf(tg, thi);
-            float lo = 0.f, hi = thi;
-            bool hi_set = false;
-            int state = kRowDefer, cnt = 0;
-            for (int it = 0; it < kKnnIter; ++it) {
-                cnt = count_below<DIM, NS>(d2, T);
-                if (cnt >= k && cnt <= kWave) {
-                    state = kRowFull;
-                    break;
-                }
-                if (cnt < k) {
-                    if (T >= thi) {
-                        state = blk ? kRowDefer : kRowShort;
-                        break;
-                    }
-                    lo = T;
-                    T = hi_set ? 0.5f * (T + hi) : fminf(fmaxf(T * 1.5f, 1e-3f * K.t0), thi);
-                } else {
-                    hi = T;
-                    hi_set = true;
-                    T = 0.5f * (lo + T);
-                }
-            }
+            int cnt = 0;
+            const int state = find_threshold<DIM, NS>(K, d2, thi, blk, T, cnt);
             if (state == kRowDefer) {
                 defer |= 1ull << t;
                 continue;
             }
-            // compact the candidates under T (the rest of the buffer holds
-            // keys that sort last) and rank them
-            W.key[lane] = kNoKey;
-            int nb = 0;
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const bool h = d2[s] < T;
-                const unsigned long long m = __ballot(h);
-                if (h) W.key[nb + (int)lane_prefix(m)] = knn_key(d2[s], c.id[s]);
-                nb += __popcll(m);
-            }
-            wave_sync();
-            // Each key is ranked by one lane of every group of gsz >= cnt
-            // lanes; the groups split the buffer between them (four keys per
-            // step, independent LDS reads) and their partial ranks are summed
-            // across groups.  Past cnt the buffer holds keys that sort last.
-            const int gsz = cnt <= 16 ? 16 : (cnt <= 32 ? 32 : kWave);
-            const int ng = kWave / gsz;
-            const int share = ((cnt + ng - 1) / ng + 3) & ~3;
-            const unsigned long long mine = W.key[lane & (gsz - 1)];
-            const unsigned long long* part = &W.key[(lane / gsz) * share];
-            int r = 0;
-            for (int u = 0; u < share; u += 4) {
-                const ulonglong2 a2 = *reinterpret_cast<const ulonglong2*>(&part[u]);
-                const ulonglong2 b2 = *reinterpret_cast<const ulonglong2*>(&part[u + 2]);
-                r += (a2.x < mine ? 1 : 0) + (a2.y < mine ? 1 : 0) + (b2.x < mine ? 1 : 0) +
-                     (b2.y < mine ? 1 : 0);
-            }
-            if (gsz <= 32) r = pair_sum32(r);
-            if (gsz <= 16) r = pair_sum16(r);
-            const int len = state == kRowFull ? k : cnt;
-            if (lane < cnt && r < len) {
-                const long long o = (long long)k * qid + r;
-                a.out_idx[o] = (int)(unsigned)mine;
-                if (a.out_dist) a.out_dist[o] = fast_sqrt(key_d2(mine));
-            }
+            unsigned long long mine;
+            int len;
+            const int r = emit_row<DIM, NS>(a, W.key, d2, c.id, T, state, cnt, qid, lane, mine, len);
             if (state == kRowFull) {
                 const unsigned long long km = __ballot(lane < cnt && r == k - 1);
                 const float kd2 = key_d2(lane_of64((long long)mine, __ffsll((long long)km) - 1));
@@ -282,12 +301,31 @@ __global__ void __launch_bounds__(kBlock, 6) knn_kernel(const KnnArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Deferred queries: one wavefront per query, growing shells of cells.
+// Deferred queries, one wavefront per query: the block two cells around the
+// home cell first, at once; growing shells of cells for what it leaves.
 // ---------------------------------------------------------------------------
+constexpr int kFarSlots = 12;   // register slots of the block's candidates (768)
+constexpr int kFarCells = 125;  // cells of the block in 3D (25 in 2D)
+
 struct FarLds {
-    unsigned long long best[kWave];  // the best keys so far, sorted
+    alignas(16) unsigned long long best[kWave];  // the best keys so far, sorted
     unsigned long long fresh[kWave]; // keys of one batch that beat the k-th
+    // candidate p's cell of the block: bit p of mask[p / 64] marks a
+    // non-empty cell whose candidates start at p, rank[r] is the r-th of them
+    float4 off[kFarCells];           // cell offset
+    int base[kFarCells];             // first sorted position of the cell, less its start
+    unsigned long long mask[kFarSlots];
+    unsigned char rank[kFarCells];
 };
+
+// Offset of a cell (dx, dy, dz) cells from the home cell, rounded once.
+__device__ __forceinline__ float4 far_offset(const KnnGeom& K, const PairGeom& G, int dx, int dy,
+                                             int dz)
+{
+    const double fx = (double)dx / G.n[0], fy = (double)dy / G.n[1], fz = (double)dz / G.n[2];
+    return make_float4((float)(K.M[0][0] * fx + K.M[0][1] * fy + K.M[0][2] * fz),
+                       (float)(K.M[1][1] * fy + K.M[1][2] * fz), (float)(K.M[2][2] * fz), 0.f);
+}
 
 __device__ __forceinline__ int wrap(int c, int n)
 {
@@ -319,6 +357,82 @@ __device__ __forceinline__ void merge_batch(FarLds& W, unsigned long long m,
     wave_sync();
 }
 
+// One deferred query against the block two cells around its home cell, all
+// its candidates in register slots, by the common path's selection; false
+// when they do not fit or the block does not settle the row.  The cells'
+// starts are read by the lanes together: walking the block cell by cell (a
+// dependent chain of reads per cell) took 137 us for the deferred queries of
+// a 500,009-point fluid at k = 12, this 15 us.
+template <int DIM>
+__device__ __forceinline__ bool far_block(const KnnArgs& a, FarLds& W, int hx, int hy, int hz,
+                                          float qx, float qy, float qz, int qid, int lane)
+{
+    const KnnGeom& K = a.knn;
+    const PairGeom& G = a.geom;
+    constexpr int NC = DIM == 3 ? kFarCells : 25;
+    if (lane < kFarSlots) W.mask[lane] = 0ull;
+    wave_sync();
+    int C = 0, filled = 0;  // candidates and non-empty cells so far
+    for (int c0 = 0; c0 < NC; c0 += kWave) {
+        const int c = c0 + lane;
+        int cnt = 0, st = 0;
+        if (c < NC) {
+            const int dx = c % 5 - 2, dy = (c / 5) % 5 - 2, dz = DIM == 3 ? c / 25 - 2 : 0;
+            const int cell = (wrap(hz + dz, G.n[2]) * G.n[1] + wrap(hy + dy, G.n[1])) * G.n[0] +
+                             wrap(hx + dx, G.n[0]);
+            st = a.cand_start[cell];
+            cnt = a.cand_start[cell + 1] - st;
+            W.off[c] = far_offset(K, G, dx, dy, dz);
+        }
+        const int incl = wave_incl_scan(cnt);
+        const int p = C + incl - cnt;
+        const unsigned long long ne = __ballot(cnt > 0);
+        if (cnt > 0) {
+            W.base[c] = st - p;
+            W.rank[filled + (int)lane_prefix(ne)] = (unsigned char)c;
+            if (p < kFarSlots * kWave) atomicOr(&W.mask[p >> 6], 1ull << (p & 63));
+        }
+        filled += __popcll(ne);
+        C += lane_of(incl, kWave - 1);
+    }
+    wave_sync();
+    if (C > kFarSlots * kWave) return false;
+    float d2[kFarSlots];
+    int id[kFarSlots];
+    int before = 0;
+#pragma unroll
+    for (int s = 0; s < kFarSlots; ++s) {
+        d2[s] = kFar;
+        id[s] = -1;
+        const int k = s * kWave + lane;
+        const unsigned long long m = uniform64(W.mask[s]);
+        if (k < C) {
+            const int j = W.rank[lane_slot(m >> 1, before + (int)(m & 1ull) - 1)];
+            const float4 v = a.cand[W.base[j] + k];
+            const float4 o = W.off[j];
+            id[s] = __float_as_int(v.w);
+            if (!(K.excl && id[s] == qid))
+                d2[s] = dist2<DIM>(v.x + o.x - qx, v.y + o.y - qy, v.z + o.z - qz);
+        }
+        before += __popcll(m);
+    }
+    const float rb2 = guaranteed_r2<DIM>(K, qx, qy, qz, 2.f);
+    const float thi = fminf(rb2, K.lim2);
+    float T = fminf(K.t0, thi);
+    int cnt = 0;
+    const int state = find_threshold<DIM, kFarSlots>(K, d2, thi, rb2 < K.lim2 ? 1 : 0, T, cnt);
+    if (state == kRowDefer) return false;
+    unsigned long long mine;
+    int len;
+    (void)emit_row<DIM, kFarSlots>(a, W.best, d2, id, T, state, cnt, qid, lane, mine, len);
+    if (lane == 0) {
+        if (a.row_len) a.row_len[qid] = len;
+        if (!K.guard && len < expected_len(K, qid)) atomicOr(a.status, kStatusRange);
+    }
+    wave_sync();
+    return true;
+}
+
 template <int DIM>
 __global__ void __launch_bounds__(kBlock) knn_far_kernel(const KnnArgs a)
 {
@@ -341,6 +455,7 @@ __global__ void __launch_bounds__(kBlock) knn_far_kernel(const KnnArgs a)
         const int hx = home % G.n[0];
         const int hy = (home / G.n[0]) % G.n[1];
         const int hz = home / (G.n[0] * G.n[1]);
+        if (far_block<DIM>(a, W, hx, hy, hz, qx, qy, qz, qid, lane)) continue;
         int cnt = 0;
         unsigned long long kth = kNoKey;
         for (int s = 1; s <= K.smax; ++s) {
@@ -355,11 +470,7 @@ __global__ void __launch_bounds__(kBlock) knn_far_kernel(const KnnArgs a)
                         const int cell =
                             (wrap(hz + dz, G.n[2]) * G.n[1] + wrap(hy + dy, G.n[1])) * G.n[0] +
                             wrap(hx + dx, G.n[0]);
-                        const double fx = (double)dx / G.n[0], fy = (double)dy / G.n[1],
-                                     fz = (double)dz / G.n[2];
-                        const float ox = (float)(K.M[0][0] * fx + K.M[0][1] * fy + K.M[0][2] * fz);
-                        const float oy = (float)(K.M[1][1] * fy + K.M[1][2] * fz);
-                        const float oz = (float)(K.M[2][2] * fz);
+                        const float4 o = far_offset(K, G, dx, dy, dz);
                         const int b = a.cand_start[cell], e = a.cand_start[cell + 1];
                         for (int j0 = b; j0 < e; j0 += kWave) {
                             const int j = j0 + lane;
@@ -368,7 +479,7 @@ __global__ void __launch_bounds__(kBlock) knn_far_kernel(const KnnArgs a)
                                 const float4 v = a.cand[j];
                                 const int id = __float_as_int(v.w);
                                 const float d2 =
-                                    dist2<DIM>(v.x + ox - qx, v.y + oy - qy, v.z + oz - qz);
+                                    dist2<DIM>(v.x + o.x - qx, v.y + o.y - qy, v.z + o.z - qz);
                                 if (d2 < K.lim2 && !(K.excl && id == qid)) key = knn_key(d2, id);
                             }
                             const unsigned long long m =

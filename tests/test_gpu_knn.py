@@ -238,3 +238,20 @@ def test_non_finite_input_is_reported(ppa):
     with pytest.raises(ppa.PPAError) as e:
         ppa.query_knn(_box(s), pts, 6)
     assert e.value.code == ppa.PPA_ENONFINITE
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n,k", [(60, 8), (300, 12), (1500, 3), (1500, 24), (5000, 12), (5000, 64)])
+def test_deferred_queries_and_their_block(ppa, dim, n, k):
+    """Uniform points, where some rows need more than the 27-cell block: grids
+    narrower than the five-cell block, blocks of few candidates and of more
+    than its register slots hold (k = 64), rows at k = 64 keys."""
+    tilt = (0.2, -0.1, 0.15) if dim == 3 else (0.2, 0.0, 0.0)
+    s = workloads.uniform(n, 0.9, seed=40 + n + k, dim=dim, tilt=tilt)
+    idx, r2, ln = _oracle(s, k)
+    half = 0.5 * min(_box(s).widths()[:dim])
+    if not np.all(r2[:, k - 1] < (0.99 * half) ** 2):
+        pytest.skip("a k-th neighbour near half the box: no row is defined there")
+    nl = ppa.query_knn(_box(s), s.points, k)
+    _check_csr(nl, n, k)
+    check_knn_rows(nl, idx, r2, ln, range(n), k)
