@@ -18,8 +18,9 @@
 // float64 from the stored cell-local coordinates and a float64 stencil
 // offset, so the distance entering the Gaussian is exact to the rounding of
 // the stored coordinates; the window terms are then evaluated in float32
-// with the hardware exp2.  The forward adds each term into a float64 LDS
-// histogram per workgroup (partials summed by a second kernel); the adjoint
+// with the hardware exp2.  The forward adds each term into a per-wavefront LDS
+// histogram in fixed point and folds that into a float64 one per workgroup
+// (partials summed by a second kernel); the adjoint
 // gathers each query's row in float64, so every particle's gradient is
 // written once, by the wavefront that owns it, with no atomics.  The
 // adjoint recomputes the pairs instead of reading anything stored by the
@@ -41,6 +42,20 @@ struct SmoothLds {
     float4 q[kWave];   // the query chunk: cell-local xyz, index bits
     StencilLds st;
 };
+
+// Fixed-point forward histogram.  float64 LDS atomics run at about 1.4 lanes
+// a clock per CU whatever the addresses (44 cycles for a wavefront's), 32-bit
+// integer ones at about 8: a term, a float32 below 2^e, is held as two 20-bit
+// limbs, floor(v 2^(20-e)) and the next 20 bits, added by two integer atomics
+// (2^(e-40) resolution, 4.5e-13 of the largest term).  A pair adds at most
+// one term to a bin, so after kSmFold pairs the limbs, below 2^20 each, are
+// folded into the float64 histogram before a sum can pass 2^32.
+// 131,072 points, 21 bins a window: 374 us with float64 atomics, 340 now,
+// bound by vector issue (950 instructions a particle, half of them the
+// window terms).
+constexpr int kSmFold = 4000;
+constexpr int kSmFixedBins = 1024;  // limbs of more bins would cost resident workgroups
+static_assert(kSmFold <= 4095, "sums of 20-bit limbs must stay below 2^32");
 
 struct SmoothShared {
     float4 off[27];
@@ -111,10 +126,11 @@ __device__ __forceinline__ void window(const SmoothArgs& a, double r, int& b0, i
 template <int DIM, int NS>
 __device__ __forceinline__ int buffer_query(const SmSlots<DIM, NS>& c, SmoothLds& W, int nh,
                                             float qx, float qy, float qz, int qpos, int t,
-                                            float r2s)
+                                            float r2s, int left)
 {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
+        if (s * kWave >= left) break;  // the last chunk may leave slots empty
         const bool h = dist2<DIM>(c.x[s] - qx, c.y[s] - qy, c.z[s] - qz) < r2s && c.idx[s] != qpos;
         const unsigned long long m = __ballot(h);
         if (h) W.hit[nh + (int)lane_prefix(m)] = make_int2(c.idx[s], c.j[s] | (t << 5));
@@ -123,10 +139,12 @@ __device__ __forceinline__ int buffer_query(const SmSlots<DIM, NS>& c, SmoothLds
     return nh;
 }
 
-// Forward flush: every buffered pair's window terms into the LDS histogram.
-template <int DIM>
+// Forward flush: every buffered pair's window terms, into the wavefront's
+// fixed-point limbs (FIXED) or the float64 LDS histogram.
+template <int DIM, bool FIXED>
 __device__ __forceinline__ void flush_fwd(const SmoothArgs& a, const SmoothShared& L,
-                                          SmoothLds& W, double* hist, int nh, int lane)
+                                          SmoothLds& W, double* hist, unsigned* limbs, int nh,
+                                          int lane)
 {
     wave_sync();
     const float drf = (float)a.dr;
@@ -137,16 +155,47 @@ __device__ __forceinline__ void flush_fwd(const SmoothArgs& a, const SmoothShare
         int b0, b1;
         float u0;
         window(a, r, b0, b1, u0);
-        // each lane starts its walk at a different bin of its window, so the
-        // lanes of one instruction rarely add to the same bin
         const int nb = b1 - b0 + 1;
-        int m = nb > 0 ? lane % nb : 0;
+        if constexpr (FIXED) {
+            unsigned* hi = limbs + b0;
+            unsigned* lo = hi + a.bins;
+            float m = 0.f;
 #pragma unroll 4
-        for (int j = 0; j < nb; ++j) {
-            const float u = fmaf((float)m, drf, u0);
-            const float v = a.hscale * __builtin_amdgcn_exp2f(-(u * u) * a.k2);
-            atomicAdd(&hist[b0 + m], (double)v);
-            m = m + 1 == nb ? 0 : m + 1;
+            for (int j = 0; j < nb; ++j) {
+                const float u = fmaf(m, drf, u0);
+                // hfix is hscale times a power of two: the same rounding
+                const float v = a.hfix * __builtin_amdgcn_exp2f(-(u * u) * a.k2);
+                atomicAdd(&hi[j], (unsigned)v);
+                atomicAdd(&lo[j], (unsigned)(__builtin_amdgcn_fractf(v) * 1048576.f));
+                m += 1.f;
+            }
+        } else {
+            // each lane starts its walk at a different bin of its window, so the
+            // lanes of one instruction rarely add to the same bin
+            int m = nb > 0 ? lane % nb : 0;
+#pragma unroll 4
+            for (int j = 0; j < nb; ++j) {
+                const float u = fmaf((float)m, drf, u0);
+                const float v = a.hscale * __builtin_amdgcn_exp2f(-(u * u) * a.k2);
+                atomicAdd(&hist[b0 + m], (double)v);
+                m = m + 1 == nb ? 0 : m + 1;
+            }
+        }
+    }
+    wave_sync();
+}
+
+// Folds the wavefront's limbs into the float64 histogram and clears them.
+__device__ __forceinline__ void fold_limbs(const SmoothArgs& a, double* hist, unsigned* limbs,
+                                           int lane)
+{
+    wave_sync();
+    for (int b = lane; b < a.bins; b += kWave) {
+        const unsigned hi = limbs[b], lo = limbs[a.bins + b];
+        if (hi | lo) {
+            atomicAdd(&hist[b], fma((double)hi, 1048576.0, (double)lo) * a.hunit);
+            limbs[b] = 0u;
+            limbs[a.bins + b] = 0u;
         }
     }
     wave_sync();
@@ -208,10 +257,12 @@ __device__ __forceinline__ void flush_bwd(const SmoothArgs& a, const SmoothShare
     wave_sync();
 }
 
-template <int DIM, bool BWD>
+template <int DIM, bool BWD, bool FIXED>
 __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
 {
-    extern __shared__ double s_dyn[];  // forward: histogram (float64); adjoint: G (float32)
+    // forward: histogram (float64), then with FIXED two limbs per bin and
+    // wavefront; adjoint: G (float32)
+    extern __shared__ double s_dyn[];
     __shared__ SmoothShared L;
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = uniform(threadIdx.x / kWave);
@@ -230,6 +281,12 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
         else
             hist[b] = 0.0;
     }
+    unsigned* limbs = nullptr;
+    if (FIXED) {
+        unsigned* all = reinterpret_cast<unsigned*>(hist + a.bins);
+        for (int b = threadIdx.x; b < 2 * kWavesPerBlock * a.bins; b += kBlock) all[b] = 0u;
+        limbs = all + (size_t)wv * 2 * a.bins;
+    }
     __syncthreads();
     const PairIn in{a.cand, a.cand_start, a.cand, a.cand_start};
     const float r2s = G.r2max;
@@ -238,6 +295,16 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
     int t0, t1, stride;
     wave_tiles_interleaved<kWavesPerBlock>(G.ncells * a.split, wv, t0, t1, stride);
     int nh = 0;
+    int added = 0;  // pairs in the limbs
+    auto flush = [&]() {
+        if (FIXED && added + nh > kSmFold) {
+            fold_limbs(a, hist, limbs, lane);
+            added = 0;
+        }
+        flush_fwd<DIM, FIXED>(a, L, W, hist, limbs, nh, lane);
+        added += nh;
+        nh = 0;
+    };
     for (int unit = t0; unit < t1; unit += stride) {
         const int tile = unit / a.split, part = unit - tile * a.split;
         const int qa = in.q_start[tile], qb = in.q_start[tile + 1];
@@ -256,7 +323,7 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
                 for (int t = 0; t < Q.n; ++t) {
                     const float qx = lane_off(Q.q.x, t), qy = lane_off(Q.q.y, t);
                     const float qz = DIM == 3 ? lane_off(Q.q.z, t) : 0.f;
-                    nh = buffer_query<DIM, kSmSlots>(c, W, nh, qx, qy, qz, c0 + t, t, r2s);
+                    nh = buffer_query<DIM, kSmSlots>(c, W, nh, qx, qy, qz, c0 + t, t, r2s, C - k0);
                     if (BWD && nh > 0) {
                         double sx = 0.0, sy = 0.0, sz = 0.0;
                         flush_bwd<DIM>(a, L, W, Gs, nh, lane, sx, sy, sz);
@@ -267,8 +334,7 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
                             gz += sz;
                         }
                     } else if (nh >= kSmFlushAt) {
-                        flush_fwd<DIM>(a, L, W, hist, nh, lane);
-                        nh = 0;
+                        flush();
                     }
                 }
             }
@@ -280,13 +346,13 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
                     a.grad[3 * (size_t)id + 2] = DIM == 3 ? (float)gz : 0.f;
                 }
             } else if (nh > 0) {
-                flush_fwd<DIM>(a, L, W, hist, nh, lane);  // the query chunk is about to change
-                nh = 0;
+                flush();  // the query chunk is about to change
             }
             wave_sync();
         }
     }
     if (!BWD) {
+        if (FIXED) fold_limbs(a, hist, limbs, lane);
         __syncthreads();
         double* out = a.partial + (size_t)blockIdx.x * a.bins;
         for (int b = threadIdx.x; b < a.bins; b += kBlock) out[b] = hist[b];
@@ -301,20 +367,40 @@ __global__ void __launch_bounds__(256) smooth_reduce_kernel(const double* __rest
     const int b = blockIdx.x * 256 + threadIdx.x;
     if (b >= bins) return;
     double sum = 0.0;
+#pragma unroll 16
     for (int g = 0; g < rows; ++g) sum += level2[(size_t)g * bins + b];
     h[b] += sum;
 }
 
-template <int DIM, bool BWD>
+template <int DIM, bool BWD, bool FIXED>
 int occupancy_blocks(size_t dyn)
 {
     const int cus = device_cus();
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, smooth_kernel<DIM, BWD>, kBlock,
-                                                     dyn) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, smooth_kernel<DIM, BWD, FIXED>,
+                                                     kBlock, dyn) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
     return (cus * per_cu + 7) / 8 * 8;
+}
+
+bool fixed_bins(int bins) { return bins <= kSmFixedBins; }
+
+size_t fwd_lds(int bins)
+{
+    return (sizeof(double) + (fixed_bins(bins) ? 2 * kWavesPerBlock * sizeof(unsigned) : 0)) *
+           (size_t)bins;
+}
+
+template <int DIM>
+void launch_fwd_dim(const SmoothArgs& a, int blocks, hipStream_t s)
+{
+    const size_t dyn = fwd_lds(a.bins);
+    if (fixed_bins(a.bins))
+        hipLaunchKernelGGL((smooth_kernel<DIM, false, true>), dim3(blocks), dim3(kBlock), dyn, s, a);
+    else
+        hipLaunchKernelGGL((smooth_kernel<DIM, false, false>), dim3(blocks), dim3(kBlock), dyn, s,
+                           a);
 }
 
 }  // namespace
@@ -323,19 +409,25 @@ int occupancy_blocks(size_t dyn)
 // sized by it): every workgroup the device holds at once, a multiple of 8.
 int smooth_workgroups(bool adjoint, int dim, int bins)
 {
-    const size_t dyn = (adjoint ? sizeof(float) : sizeof(double)) * (size_t)bins;
-    if (dim == 3)
-        return adjoint ? occupancy_blocks<3, true>(dyn) : occupancy_blocks<3, false>(dyn);
-    return adjoint ? occupancy_blocks<2, true>(dyn) : occupancy_blocks<2, false>(dyn);
+    if (adjoint) {
+        const size_t dyn = sizeof(float) * (size_t)bins;
+        return dim == 3 ? occupancy_blocks<3, true, false>(dyn)
+                        : occupancy_blocks<2, true, false>(dyn);
+    }
+    const size_t dyn = fwd_lds(bins);
+    if (fixed_bins(bins))
+        return dim == 3 ? occupancy_blocks<3, false, true>(dyn)
+                        : occupancy_blocks<2, false, true>(dyn);
+    return dim == 3 ? occupancy_blocks<3, false, false>(dyn)
+                    : occupancy_blocks<2, false, false>(dyn);
 }
 
 void launch_smooth_fwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s)
 {
-    const size_t dyn = sizeof(double) * (size_t)a.bins;
     if (dim == 3)
-        hipLaunchKernelGGL((smooth_kernel<3, false>), dim3(blocks), dim3(kBlock), dyn, s, a);
+        launch_fwd_dim<3>(a, blocks, s);
     else
-        hipLaunchKernelGGL((smooth_kernel<2, false>), dim3(blocks), dim3(kBlock), dyn, s, a);
+        launch_fwd_dim<2>(a, blocks, s);
     const int rows = partial_rows(blocks);
     hipLaunchKernelGGL(partial_sum_stage1<double>, dim3((a.bins + 63) / 64, rows), dim3(256), 0, s,
                        a.partial, blocks, a.bins, kPartialRowsPer, a.level2);
@@ -347,9 +439,9 @@ void launch_smooth_bwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s)
 {
     const size_t dyn = sizeof(float) * (size_t)a.bins;
     if (dim == 3)
-        hipLaunchKernelGGL((smooth_kernel<3, true>), dim3(blocks), dim3(kBlock), dyn, s, a);
+        hipLaunchKernelGGL((smooth_kernel<3, true, false>), dim3(blocks), dim3(kBlock), dyn, s, a);
     else
-        hipLaunchKernelGGL((smooth_kernel<2, true>), dim3(blocks), dim3(kBlock), dyn, s, a);
+        hipLaunchKernelGGL((smooth_kernel<2, true, false>), dim3(blocks), dim3(kBlock), dyn, s, a);
 }
 
 }  // namespace ppa
