@@ -895,6 +895,7 @@ struct SmoothPlan {
     Grid g;
     double r_s;  // pair cutoff r_max + 8 sigma
     int blocks;
+    int nodes;   // adjoint: table nodes, sigma / 16 apart (0: too many, no table)
 };
 
 int smooth_plan(const BoxPrep& bp, int64_t n, int32_t bins, float r_max, float sigma, bool adjoint,
@@ -908,15 +909,19 @@ int smooth_plan(const BoxPrep& bp, int64_t n, int32_t bins, float r_max, float s
     int rc;
     if ((rc = check_cutoff(bp, P->r_s))) return rc;
     make_grid(bp, P->r_s, n, &P->g);
-    P->blocks = smooth_workgroups(adjoint, bp.dim, bins);
+    const double nodes = ceil(P->r_s / ((double)sigma / 16.0)) + 2.0;
+    P->nodes = adjoint && nodes <= kSmoothMaxNodes ? (int)nodes : 0;
+    P->blocks = smooth_workgroups(adjoint, bp.dim, bins, P->nodes > 0);
     return PPA_OK;
 }
 
 size_t smooth_layout(const SmoothPlan& P, int64_t n, int32_t bins, void* base_v, Workspace* W,
-                     double** partial, double** level2)
+                     double** partial, double** level2, float4** table)
 {
     char* base = (char*)base_v;
     size_t off = workspace_layout(P.g, n, 0, 0, base_v, W);
+    *table = base ? (float4*)(base + off) : nullptr;
+    off = (off + sizeof(float4) * (size_t)P.nodes + 255) & ~(size_t)255;
     *partial = base ? (double*)(base + off) : nullptr;
     off = (off + sizeof(double) * (size_t)P.blocks * (size_t)bins + 255) & ~(size_t)255;
     *level2 = base ? (double*)(base + off) : nullptr;
@@ -941,11 +946,12 @@ int run_smooth(const ppa_box* box, const float* pts, int64_t n, int32_t bins, fl
     Workspace W{};
     double* partial = nullptr;
     double* level2 = nullptr;
-    const size_t need = smooth_layout(P, n, bins, nullptr, &W, &partial, &level2);
+    float4* table = nullptr;
+    const size_t need = smooth_layout(P, n, bins, nullptr, &W, &partial, &level2, &table);
     if (!ws || ((uintptr_t)ws & 255) || ws_bytes < need)
         return set_error(PPA_EWORKSPACE, "workspace needs %zu bytes, 256-byte aligned (got %zu)",
                          need, ws_bytes);
-    smooth_layout(P, n, bins, ws, &W, &partial, &level2);
+    smooth_layout(P, n, bins, ws, &W, &partial, &level2, &table);
     if (n == 0) return PPA_OK;
     const Grid& g = P.g;
     launch_zero(W, g, false, nullptr, 0, s);
@@ -987,6 +993,11 @@ int run_smooth(const ppa_box* box, const float* pts, int64_t n, int32_t bins, fl
     A.hfix = ldexpf(A.hscale, 20 - e);
     A.hunit = ldexp(1.0, e - 40);
     A.gscale = (float)(A.dr / (sg * sg * sg * sqrt(2.0 * M_PI)));
+    A.table = table;
+    A.nodes = P.nodes;
+    A.node_w = sg / 16.0;
+    A.inv_node_w = 16.0 / sg;
+    A.tscale = -2.0 * A.dr / (sg * sg * sqrt(2.0 * M_PI));
     A.partial = partial;
     A.level2 = level2;
     A.h = h;
@@ -1475,8 +1486,9 @@ int ppa_smooth_rdf_workspace_bytes(const ppa_box* box, int64_t n, int32_t bins, 
     Workspace W{};
     double* partial = nullptr;
     double* level2 = nullptr;
-    const size_t a = smooth_layout(P, n, bins, nullptr, &W, &partial, &level2);
-    const size_t b = smooth_layout(Pb, n, bins, nullptr, &W, &partial, &level2);
+    float4* table;
+    const size_t a = smooth_layout(P, n, bins, nullptr, &W, &partial, &level2, &table);
+    const size_t b = smooth_layout(Pb, n, bins, nullptr, &W, &partial, &level2, &table);
     *bytes = a > b ? a : b;
     return PPA_OK;
 }

@@ -400,6 +400,7 @@ void launch_knn_list(const KnnListArgs& a, int blocks, hipStream_t s);
 
 // Gaussian-smoothed RDF and its adjoint (smooth.hip).
 constexpr int kSmoothMaxBins = 4096;
+constexpr int kSmoothMaxNodes = 65536;  // of the adjoint's table (1 MiB)
 
 struct SmoothArgs {
     const float4* cand;       // points sorted by cell (they are also the queries)
@@ -421,10 +422,14 @@ struct SmoothArgs {
     double* level2;           // forward: [ceil(gridDim.x / 32)][bins] first-stage sums
     double* h;                // forward: [bins], accumulated
     const double* grad_h;     // adjoint: dL/dh [bins]
+    float4* table;            // adjoint: [nodes] Taylor coefficients of -2 A at r = i node_w
+    int nodes;                // 0: window terms instead of the table
+    double node_w, inv_node_w;
+    double tscale;            // -2 dr / (sigma^2 sqrt(2 pi)): table weight of the window sums
     float* grad;              // adjoint: dL/dp [n][3], written
 };
 
-int smooth_workgroups(bool adjoint, int dim, int bins);
+int smooth_workgroups(bool adjoint, int dim, int bins, bool table);
 void launch_smooth_fwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s);
 void launch_smooth_bwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s);
 

@@ -22,9 +22,12 @@
 // histogram in fixed point and folds that into a float64 one per workgroup
 // (partials summed by a second kernel); the adjoint
 // gathers each query's row in float64, so every particle's gradient is
-// written once, by the wavefront that owns it, with no atomics.  The
-// adjoint recomputes the pairs instead of reading anything stored by the
-// forward.
+// written once, by the wavefront that owns it, with no atomics.  For given
+// G, A(r) is one smooth function of r for every pair: a small kernel tabulates
+// it with three derivatives at nodes sigma / 16 apart (Hermite functions of
+// the window terms, summed in float64), and a pair takes one 16-byte read and
+// a cubic instead of its window's terms.  The adjoint recomputes the pairs
+// instead of reading anything stored by the forward.
 #include "pair_common.hpp"
 
 namespace ppa {
@@ -37,8 +40,9 @@ constexpr int kSmSlots = 8;   // candidate slots per chunk
 constexpr int kSmBuf = 768;   // hits buffered per wavefront
 constexpr int kSmFlushAt = kSmBuf - kSmSlots * kWave;
 
+template <int BUF>
 struct SmoothLds {
-    int2 hit[kSmBuf];  // (sorted candidate index, stencil slot | query lane << 5)
+    int2 hit[BUF];  // (sorted candidate index, stencil slot | query lane << 5)
     float4 q[kWave];   // the query chunk: cell-local xyz, index bits
     StencilLds st;
 };
@@ -57,10 +61,11 @@ constexpr int kSmFold = 4000;
 constexpr int kSmFixedBins = 1024;  // limbs of more bins would cost resident workgroups
 static_assert(kSmFold <= 4095, "sums of 20-bit limbs must stay below 2^32");
 
+template <int BUF>
 struct SmoothShared {
     float4 off[27];
     double offd[27][3];
-    SmoothLds w[kWavesPerBlock];
+    SmoothLds<BUF> w[kWavesPerBlock];
 };
 
 // Candidates [k0, k0 + 64 NS) of a stencil: coordinates relative to the
@@ -97,9 +102,9 @@ struct SmSlots {
 };
 
 // Pair vector of a buffered hit in float64, candidate minus query.
-template <int DIM>
-__device__ __forceinline__ void hit_vector(const SmoothArgs& a, const SmoothShared& L,
-                                           const SmoothLds& W, int2 h, double& dx, double& dy,
+template <int DIM, int BUF>
+__device__ __forceinline__ void hit_vector(const SmoothArgs& a, const SmoothShared<BUF>& L,
+                                           const SmoothLds<BUF>& W, int2 h, double& dx, double& dy,
                                            double& dz)
 {
     const int j = h.y & 31;
@@ -123,8 +128,8 @@ __device__ __forceinline__ void window(const SmoothArgs& a, double r, int& b0, i
 }
 
 // Hits of query t (scalar) against NS slots, appended to the buffer.
-template <int DIM, int NS>
-__device__ __forceinline__ int buffer_query(const SmSlots<DIM, NS>& c, SmoothLds& W, int nh,
+template <int DIM, int NS, int BUF>
+__device__ __forceinline__ int buffer_query(const SmSlots<DIM, NS>& c, SmoothLds<BUF>& W, int nh,
                                             float qx, float qy, float qz, int qpos, int t,
                                             float r2s, int left)
 {
@@ -141,16 +146,16 @@ __device__ __forceinline__ int buffer_query(const SmSlots<DIM, NS>& c, SmoothLds
 
 // Forward flush: every buffered pair's window terms, into the wavefront's
 // fixed-point limbs (FIXED) or the float64 LDS histogram.
-template <int DIM, bool FIXED>
-__device__ __forceinline__ void flush_fwd(const SmoothArgs& a, const SmoothShared& L,
-                                          SmoothLds& W, double* hist, unsigned* limbs, int nh,
+template <int DIM, bool FIXED, int BUF>
+__device__ __forceinline__ void flush_fwd(const SmoothArgs& a, const SmoothShared<BUF>& L,
+                                          SmoothLds<BUF>& W, double* hist, unsigned* limbs, int nh,
                                           int lane)
 {
     wave_sync();
     const float drf = (float)a.dr;
     for (int e = lane; e < nh; e += kWave) {
         double dx, dy, dz;
-        hit_vector<DIM>(a, L, W, W.hit[e], dx, dy, dz);
+        hit_vector<DIM, BUF>(a, L, W, W.hit[e], dx, dy, dz);
         const double r = sqrt(fma(dz, dz, fma(dy, dy, dx * dx)));
         int b0, b1;
         float u0;
@@ -208,10 +213,55 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Adjoint flush for the hits of one query: the sum of -2 A(r) d / r.
-template <int DIM>
-__device__ __forceinline__ void flush_bwd(const SmoothArgs& a, const SmoothShared& L,
-                                          SmoothLds& W, const float* G, int nh, int lane,
+// 1 / sqrt(x) in float64 from the hardware's approximation (about 2^-23) by one
+// cubic step: relative error about 1e-16.
+__device__ __forceinline__ double inv_sqrt(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y, e * fma(e, 0.375, 0.5), y);
+}
+
+// Nodes of the table of -2 A(r): node i at r = i w, w = sigma / 16.  Row i
+// holds the Taylor coefficients in (r - i w) / sigma up to the third: the
+// remainder over half a node, (1/32)^4 / 24 times the fifth Hermite function
+// (at most about 6), is 2.4e-7 of a window term, against the few 1e-6 that
+// float32 window terms by recurrence were off.  16 lanes per node.
+__global__ void __launch_bounds__(256) smooth_table_kernel(const SmoothArgs a)
+{
+    const int node = (int)(blockIdx.x * 256 + threadIdx.x) >> 4;
+    const int l = threadIdx.x & 15;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    const double r = (double)node * a.node_w, inv_s = 8.0 / a.w8;
+    if (node < a.nodes) {
+        const int b0 = max(0, (int)ceil((r - a.w8) / a.dr - 0.5));
+        const int b1 = min(a.bins - 1, (int)floor((r + a.w8) / a.dr - 0.5));
+        for (int b = b0 + l; b <= b1; b += 16) {
+            const double t = fma((double)b + 0.5, a.dr, -r) * inv_s, t2 = t * t;
+            const double e = a.grad_h[b] * exp(-0.5 * t2);
+            s0 = fma(e, t, s0);
+            s1 = fma(e, t2 - 1.0, s1);
+            s2 = fma(e, t * (t2 - 3.0), s2);
+            s3 = fma(e, fma(t2, t2 - 6.0, 3.0), s3);
+        }
+    }
+#pragma unroll
+    for (int d = 8; d > 0; d >>= 1) {
+        s0 += __shfl_xor(s0, d);
+        s1 += __shfl_xor(s1, d);
+        s2 += __shfl_xor(s2, d);
+        s3 += __shfl_xor(s3, d);
+    }
+    if (l == 0 && node < a.nodes)
+        a.table[node] = make_float4((float)(a.tscale * s0), (float)(a.tscale * s1),
+                                    (float)(a.tscale * s2 / 2.0), (float)(a.tscale * s3 / 6.0));
+}
+
+// Adjoint flush for the hits of one query: the sum of -2 A(r) d / r, A from the
+// table (TABLE) or from its window's terms.
+template <int DIM, bool TABLE, int BUF>
+__device__ __forceinline__ void flush_bwd(const SmoothArgs& a, const SmoothShared<BUF>& L,
+                                          SmoothLds<BUF>& W, const float* G, int nh, int lane,
                                           double& gx, double& gy, double& gz)
 {
     wave_sync();
@@ -219,9 +269,19 @@ __device__ __forceinline__ void flush_bwd(const SmoothArgs& a, const SmoothShare
     double ax = 0.0, ay = 0.0, az = 0.0;
     for (int e = lane; e < nh; e += kWave) {
         double dx, dy, dz;
-        hit_vector<DIM>(a, L, W, W.hit[e], dx, dy, dz);
-        const double r = sqrt(fma(dz, dz, fma(dy, dy, dx * dx)));
-        if (r > 0.0) {
+        hit_vector<DIM, BUF>(a, L, W, W.hit[e], dx, dy, dz);
+        const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+        if (!(r2 > 0.0)) continue;
+        double f;
+        if constexpr (TABLE) {
+            const double inv_r = inv_sqrt(r2);
+            const double r = r2 * inv_r;
+            const int i = min((int)fma(r, a.inv_node_w, 0.5), a.nodes - 1);
+            const float4 c = a.table[i];
+            const float y = (float)(fma(-(double)i, a.node_w, r) * (8.0 / a.w8));
+            f = (double)fmaf(fmaf(fmaf(c.w, y, c.z), y, c.y), y, c.x) * inv_r;
+        } else {
+            const double r = sqrt(r2);
             int b0, b1;
             float u0;
             window(a, r, b0, b1, u0);
@@ -245,11 +305,11 @@ __device__ __forceinline__ void flush_bwd(const SmoothArgs& a, const SmoothShare
                 p *= c;
                 u += drf;
             }
-            const double f = -2.0 * A / r;
-            ax = fma(f, dx, ax);
-            ay = fma(f, dy, ay);
-            az = fma(f, dz, az);
+            f = -2.0 * A / r;
         }
+        ax = fma(f, dx, ax);
+        ay = fma(f, dy, ay);
+        az = fma(f, dz, az);
     }
     gx += wave_sum(ax);
     gy += wave_sum(ay);
@@ -257,16 +317,20 @@ __device__ __forceinline__ void flush_bwd(const SmoothArgs& a, const SmoothShare
     wave_sync();
 }
 
-template <int DIM, bool BWD, bool FIXED>
+// FAST: fixed-point limbs (forward), tabulated A (adjoint).
+template <int DIM, bool BWD, bool FAST>
 __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
 {
+    constexpr bool FIXED = !BWD && FAST, TABLE = BWD && FAST;
+    // the adjoint flushes after every chunk of a query
+    constexpr int BUF = BWD ? kSmSlots * kWave : kSmBuf;
     // forward: histogram (float64), then with FIXED two limbs per bin and
-    // wavefront; adjoint: G (float32)
+    // wavefront; adjoint without the table: G (float32)
     extern __shared__ double s_dyn[];
-    __shared__ SmoothShared L;
+    __shared__ SmoothShared<BUF> L;
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = uniform(threadIdx.x / kWave);
-    SmoothLds& W = L.w[wv];
+    SmoothLds<BUF>& W = L.w[wv];
     const PairGeom& G = a.geom;
     if (threadIdx.x < 27) {
         L.off[threadIdx.x] = make_float4(G.off[threadIdx.x][0], G.off[threadIdx.x][1],
@@ -275,7 +339,7 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
     }
     double* hist = s_dyn;
     float* Gs = reinterpret_cast<float*>(s_dyn);
-    for (int b = threadIdx.x; b < a.bins; b += kBlock) {
+    for (int b = threadIdx.x; b < (TABLE ? 0 : a.bins); b += kBlock) {
         if (BWD)
             Gs[b] = (float)a.grad_h[b] * a.gscale;
         else
@@ -301,7 +365,7 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
             fold_limbs(a, hist, limbs, lane);
             added = 0;
         }
-        flush_fwd<DIM, FIXED>(a, L, W, hist, limbs, nh, lane);
+        flush_fwd<DIM, FIXED, BUF>(a, L, W, hist, limbs, nh, lane);
         added += nh;
         nh = 0;
     };
@@ -323,10 +387,10 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
                 for (int t = 0; t < Q.n; ++t) {
                     const float qx = lane_off(Q.q.x, t), qy = lane_off(Q.q.y, t);
                     const float qz = DIM == 3 ? lane_off(Q.q.z, t) : 0.f;
-                    nh = buffer_query<DIM, kSmSlots>(c, W, nh, qx, qy, qz, c0 + t, t, r2s, C - k0);
+                    nh = buffer_query<DIM, kSmSlots, BUF>(c, W, nh, qx, qy, qz, c0 + t, t, r2s, C - k0);
                     if (BWD && nh > 0) {
                         double sx = 0.0, sy = 0.0, sz = 0.0;
-                        flush_bwd<DIM>(a, L, W, Gs, nh, lane, sx, sy, sz);
+                        flush_bwd<DIM, TABLE, BUF>(a, L, W, Gs, nh, lane, sx, sy, sz);
                         nh = 0;
                         if (lane == t) {
                             gx += sx;
@@ -372,12 +436,12 @@ __global__ void __launch_bounds__(256) smooth_reduce_kernel(const double* __rest
     h[b] += sum;
 }
 
-template <int DIM, bool BWD, bool FIXED>
+template <int DIM, bool BWD, bool FAST>
 int occupancy_blocks(size_t dyn)
 {
     const int cus = device_cus();
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, smooth_kernel<DIM, BWD, FIXED>,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, smooth_kernel<DIM, BWD, FAST>,
                                                      kBlock, dyn) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
@@ -407,10 +471,12 @@ void launch_fwd_dim(const SmoothArgs& a, int blocks, hipStream_t s)
 
 // Workgroups of a smoothed-RDF launch (the forward's partial histograms are
 // sized by it): every workgroup the device holds at once, a multiple of 8.
-int smooth_workgroups(bool adjoint, int dim, int bins)
+int smooth_workgroups(bool adjoint, int dim, int bins, bool table)
 {
     if (adjoint) {
         const size_t dyn = sizeof(float) * (size_t)bins;
+        if (table)
+            return dim == 3 ? occupancy_blocks<3, true, true>(0) : occupancy_blocks<2, true, true>(0);
         return dim == 3 ? occupancy_blocks<3, true, false>(dyn)
                         : occupancy_blocks<2, true, false>(dyn);
     }
@@ -437,6 +503,14 @@ void launch_smooth_fwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s)
 
 void launch_smooth_bwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s)
 {
+    if (a.nodes > 0) {
+        hipLaunchKernelGGL(smooth_table_kernel, dim3((a.nodes + 15) / 16), dim3(256), 0, s, a);
+        if (dim == 3)
+            hipLaunchKernelGGL((smooth_kernel<3, true, true>), dim3(blocks), dim3(kBlock), 0, s, a);
+        else
+            hipLaunchKernelGGL((smooth_kernel<2, true, true>), dim3(blocks), dim3(kBlock), 0, s, a);
+        return;
+    }
     const size_t dyn = sizeof(float) * (size_t)a.bins;
     if (dim == 3)
         hipLaunchKernelGGL((smooth_kernel<3, true, false>), dim3(blocks), dim3(kBlock), dyn, s, a);

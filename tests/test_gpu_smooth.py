@@ -219,3 +219,33 @@ def test_non_finite_input_is_reported(ppa):
     with pytest.raises(ppa.PPAError) as e:
         ppa.smooth_rdf_grad(_box(s), pts, BINS, R_MAX, SIGMA, np.ones(BINS))
     assert e.value.code == ppa.PPA_ENONFINITE
+
+
+@pytest.mark.parametrize("bins", [1, 63, 1024, 1025])
+def test_forward_fixed_point_limbs(ppa, bins):
+    """Few full cells, so every wavefront folds its fixed-point limbs many
+    times (over 10^5 pairs each), at bin counts around the limit of the
+    fixed-point histogram and at one bin."""
+    s = workloads.uniform(6000, 0.9, seed=91)
+    h = ppa.smooth_rdf_h(_box(s), s.points, bins, 8.0, 0.05).cpu().numpy()
+    _check_h(h, oracle.smooth_rdf_h(_obox(s), s.points, bins, 8.0, 0.05))
+
+
+@pytest.mark.parametrize("bins,r_max,sigma", [(1, 2.5, 0.05), (40, 2.5, 0.5), (100, 2.5, 0.02),
+                                              (2048, 2.5, 6.2e-4), (2048, 2.5, 6.0e-4)])
+def test_adjoint_table_and_its_limit(ppa, bins, r_max, sigma):
+    """The tabulated adjoint against the oracle from wide to narrow Gaussians,
+    on both sides of its limit of 65536 nodes (r_max / sigma about 4095)."""
+    nodes = np.ceil((r_max + 8 * np.float64(np.float32(sigma))) / (np.float32(sigma) / 16.0)) + 2
+    assert (nodes > 65536) == (sigma == 6.0e-4)
+    dim_tilt = (0.1, 0.2, -0.1)
+    s = workloads.uniform(2500, 0.9, seed=92, tilt=dim_tilt)
+    gh = np.random.default_rng(93).normal(size=bins)
+    g_ref = oracle.smooth_rdf_grad(_obox(s), s.points, bins, r_max, sigma, gh)
+    g = ppa.smooth_rdf_grad(_box(s), s.points, bins, r_max, sigma, gh).cpu().numpy()
+    # a stored coordinate is off by up to 2^-24 of its cell (under 8), a pair's
+    # distance by up to 4 of these, a term by that over sigma (times at most 2)
+    tol = GRAD_TOL + 8 * 2.0 ** -24 * 8.0 / sigma
+    d = g.astype(np.float64) - g_ref
+    assert np.linalg.norm(d) < tol * np.linalg.norm(g_ref)
+    assert np.abs(d).max() < tol * np.abs(g_ref).max()
