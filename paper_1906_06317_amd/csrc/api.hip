@@ -155,7 +155,7 @@ static void carve_cells(char* base, size_t& off, const Grid& g, int64_t n, CellL
     cl->scan_ticket = cl->scan_flags ? (int*)(cl->scan_flags + nf) : nullptr;
 }
 
-// Workspace: 256-byte header (status word, counters), the points' cell list,
+// Workspace: header (status word, counters, work queues), the points' cell list,
 // the query points' cell list when they differ, and for query-ordered rows a
 // row-count array plus the scan state for the row offsets.
 size_t workspace_layout(const Grid& g, int64_t n, int64_t nq, int32_t flags, void* base_v,
@@ -165,7 +165,8 @@ size_t workspace_layout(const Grid& g, int64_t n, int64_t nq, int32_t flags, voi
     size_t off = 0;
     ws->status = base ? (unsigned*)base : nullptr;
     ws->counters = base ? (unsigned long long*)(base + 64) : nullptr;
-    off = 256;
+    ws->queue = base ? (unsigned long long*)(base + 256) : nullptr;
+    off = kHeaderBytes;
     carve_cells(base, off, g, n, &ws->pts);
     if (nq > 0) {
         carve_cells(base, off, g, nq, &ws->qry);
@@ -350,6 +351,7 @@ int run_pairs(const QueryCall& c)
     A.geom.r2max = c.r_max * c.r_max;
     A.geom.dot = expanded_test_ok(bp, g, c.r_max) ? 1 : 0;
     A.geom.split = pair_split(g.ncells, c.nq);
+    A.geom.queue = W.queue;
     A.offsets = c.offsets;
     A.point_idx = c.point_idx;
     A.dist = c.dist;
@@ -1092,7 +1094,7 @@ int ppa_query_ball(const ppa_box* box, const float* pts, int64_t n, const float*
 // own copy of the array) and kept; host code uses only that address.
 namespace ppa {
 namespace {
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
+constexpr size_t kStaticScratchBytes = ((size_t)64 << 20) + kQueueBytes;
 constexpr int kMaxDevices = 64;
 __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 std::mutex g_scratch_mu;

@@ -107,7 +107,6 @@ struct ppa_batch_plan_s {
     int chosen;
     size_t point_base_off;
     size_t part_off;          // partial-count array of the chunked cell build
-    size_t queue_off;         // the pair passes' queue counters
     size_t scratch_hist_off;  // autotuning histograms
     size_t bytes;
     bool uploaded;
@@ -173,7 +172,7 @@ void enqueue(const ppa_batch_plan* p, int ci, const float* pts, void* ws, const 
     // scan state matches the carved layout)
     Grid g{};
     g.ncells = max_cells(p);
-    launch_zero(W, g, false, base + p->queue_off, kQueueBytes, s);
+    launch_zero(W, g, false, nullptr, 0, s);
     const FrameInfo* frames = (const FrameInfo*)(base + T.frames_off);
     const int* cell_base = (const int*)(base + T.cell_base_off);
     const int* point_base = (const int*)(base + p->point_base_off);
@@ -205,7 +204,7 @@ void enqueue(const ppa_batch_plan* p, int ci, const float* pts, void* ws, const 
     B.r2max = p->r_max * p->r_max;
     B.run = kConfigs[ci].run;
     B.split = pair_split(T.ncells, p->n_total);
-    B.queue = (unsigned long long*)(base + p->queue_off);  // cleared by launch_zero above
+    B.queue = W.queue;  // in the header, cleared by launch_zero above
     const int cap = kConfigs[ci].blocks_cap;
     const int waves = kConfigs[ci].waves;
     launch_count_batch(A, B, p->dim, p->excl, cap, waves, s);
@@ -331,8 +330,6 @@ int ppa_batch_plan_create(int32_t n_frames, const ppa_box* boxes, const int64_t*
     int64_t part = 1;
     for (int c = 0; c < kNumConfigs; ++c)
         part = p->cfg[c].part_entries > part ? p->cfg[c].part_entries : part;
-    p->queue_off = off;
-    off = align256(off + kQueueBytes);
     p->part_off = off;
     off = align256(off + sizeof(int) * (size_t)part);
     p->scratch_hist_off = off;

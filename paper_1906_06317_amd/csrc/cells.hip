@@ -509,7 +509,7 @@ void launch_zero(Workspace& ws, const Grid& g, bool separate_queries, void* extr
         z.words[z.count] = (long long)((bytes + 3) / 4);
         ++z.count;
     };
-    add(ws.status, 256);  // status word and counters share the header
+    add(ws.status, kHeaderBytes);  // status word, counters and work queues
     const size_t nf = scan_flag_count(g.ncells);
     add(ws.pts.cell_count, sizeof(int) * (size_t)g.ncells);
     add(ws.pts.scan_flags, sizeof(unsigned long long) * nf + 256);

@@ -33,10 +33,9 @@ __global__ void __launch_bounds__(kBlock, 5) fill_kernel(const PairIn in, const 
     Filler<DIM, EXCL, NL, HIST> F(s_w[wv], O, lds_hist ? s_hist : nullptr, lane);
     const GeomView V = view_of(G);
     const int split = G.split > 1 ? G.split : 1;
-    int t0, t1, stride;
-    wave_tiles_interleaved<kWavesPerBlock>(G.ncells * split, wv, t0, t1, stride);
-    for (int v = t0; v < t1; v += stride) {
-        const CellPart P = cell_part(in, v, split);
+    CellWalk<kWavesPerBlock> walk(G.ncells * split, wv, lane, G.dealt, G.queue);
+    for (int v; walk.next(v);) {
+        const CellPart P = cell_part(in, uniform(v), split);
         if (P.q0 == P.q1) continue;
         const int C = stencil<DIM>(in, V, P.tile, lane, S);
         const int ns = (C + kWave - 1) / kWave;
@@ -75,8 +74,11 @@ void launch_fill_t(const PairIn& in, const PairGeom& g, const FillOut& o, bool n
     const size_t lds = (hist && o.bins <= kMaxLdsBins) ? sizeof(unsigned) * (size_t)o.bins : 0;
     auto k = nl ? (hist ? fill_kernel<DIM, EXCL, true, true> : fill_kernel<DIM, EXCL, true, false>)
                 : fill_kernel<DIM, EXCL, false, true>;
-    const int blocks = resident_blocks(k, lds, (long long)g.ncells * (g.split > 1 ? g.split : 1));
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), lds, s, in, g, o);
+    const long long items = (long long)g.ncells * (g.split > 1 ? g.split : 1);
+    const int blocks = resident_blocks(k, lds, items);
+    PairGeom geom = g;
+    geom.dealt = dealt_rounds(items, blocks, kWavesPerBlock);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), lds, s, in, geom, o);
 }
 
 template <int DIM>

@@ -66,6 +66,7 @@ struct CellList {
 struct Workspace {
     unsigned* status;             // device status bits
     unsigned long long* counters; // [24] general counters (k-NN deferred count)
+    unsigned long long* queue;    // work queues of the pair passes (kQueueBytes)
     CellList pts;
     CellList qry;                 // == pts for self queries
     // canonical-row mode: int64 exclusive scan of row counts
@@ -112,6 +113,13 @@ constexpr int kChunkMaxCells = 32768;
 constexpr int kPartialRowsPer = 32;
 inline int partial_rows(int G) { return (G + kPartialRowsPer - 1) / kPartialRowsPer; }
 
+// Work-queue counters, 8 per-XCD ones for each of two passes, every counter
+// on its own 128-byte line (draws on one line are serialised, about 12 ns
+// each).
+constexpr int kQueueStride = 16;  // in 64-bit words
+constexpr size_t kQueueBytes = 16 * kQueueStride * sizeof(unsigned long long);
+constexpr size_t kHeaderBytes = 256 + kQueueBytes;  // workspace header, cleared by each call
+
 // Host helpers (api.hip).
 int prepare_box(const ppa_box* box, BoxPrep* out);
 int make_grid(const BoxPrep& b, double r_cut, int64_t n_hint, Grid* g);
@@ -152,6 +160,8 @@ struct PairGeom {
     float r2max;
     int dot;             // 1: expanded in/out test (its error bound passed on the host)
     int split;           // ball query: wavefronts sharing a home cell's queries (0, 1: one)
+    int dealt;           // fill pass: rounds of cells dealt in turn (set by its launch)
+    unsigned long long* queue;  // zeroed work-queue counters (fill pass)
 };
 
 struct PairArgs {
@@ -183,8 +193,6 @@ struct BatchGeom {
     int split;         // wavefronts sharing a home cell's queries (1: a work item is a cell)
     unsigned long long* queue;  // zeroed: 8 per-XCD counters per pass, kQueueStride apart
 };
-constexpr int kQueueStride = 16;  // in 64-bit words: every counter on its own 128-byte line
-constexpr size_t kQueueBytes = 16 * kQueueStride * sizeof(unsigned long long);
 // waves: wavefronts per workgroup (2 or 4)
 void launch_count_batch(const PairArgs& a, const BatchGeom& b, int dim, int excl, int blocks_cap,
                         int waves, hipStream_t s);

@@ -162,6 +162,69 @@ __device__ __forceinline__ void wave_tiles_interleaved(int ncells, int wv, int& 
     if ((int)(blockIdx.x >> 3) >= per) t1 = t0;  // launches are whole multiples of 8
 }
 
+// The same order of home cells, of which a wavefront takes the first part in
+// turn, as above, and draws the rest (one cell in four) one by one from its
+// XCD's queue: wavefronts progress unevenly, and with everything dealt in turn
+// the fill pass kept 3.7 of its 5 wavefronts per SIMD resident on average.  A
+// draw costs an atomic shared by the XCD's wavefronts (about 12 ns each), made
+// one cell ahead.  Fill pass, 2^20-point FCC: 390 us dealt, 379 with one in
+// 8 drawn, 360 with one in 4, the same with one in 2 (which took a list of
+// 7 neighbours a point, whose cells are quick, 250 -> 300 us).  The count pass
+// (8 us a cell) waits longer for its draws than they even out: 103 -> 111 us,
+// so it deals.  Under 8 rounds of cells every one is dealt: there a draw each
+// round would cost more than the unevenness.
+inline int dealt_rounds(long long items, int blocks, int wpb)
+{
+    const long long rounds = items / ((long long)blocks * wpb);
+    return rounds < 8 ? -1 : (int)(rounds - rounds / 4);
+}
+
+template <int WPB>
+struct CellWalk {
+    int c0, c1;      // this XCD's items
+    int at, stride;  // the next item dealt in turn
+    int drawn;       // first item of the queue
+    unsigned long long* queue;
+    unsigned long long pend;  // lane 0: the draw made ahead
+    int lane;
+
+    // dealt: rounds of items dealt in turn (dealt_rounds), negative for all
+    __device__ __forceinline__ CellWalk(int items, int wv, int l, int dealt,
+                                        unsigned long long* queues)
+        : pend(0), lane(l)
+    {
+        const int xcd = blockIdx.x & 7;
+        const int per = gridDim.x >> 3;  // workgroups per XCD (the grid is a multiple of 8)
+        c0 = (int)((long long)xcd * items / 8);
+        c1 = (int)((long long)(xcd + 1) * items / 8);
+        stride = per * WPB;
+        drawn = uniform(dealt < 0 ? c1 : min(c1, c0 + dealt * stride));
+        at = uniform(c0 + (blockIdx.x >> 3) * WPB + wv);
+        queue = queues + xcd * kQueueStride;
+        if (at >= drawn && drawn < c1) draw();
+    }
+    __device__ __forceinline__ void draw()
+    {
+        if (lane == 0) pend = atomicAdd(queue, 1ull);
+    }
+    // The next item v of this wavefront; false at the end.
+    __device__ __forceinline__ bool next(int& v)
+    {
+        if (at < drawn) {
+            v = at;
+            at = uniform(at + stride);
+            if (at >= drawn && drawn < c1) draw();
+            return true;
+        }
+        if (drawn >= c1) return false;
+        const unsigned long long k = uniform64(pend);
+        if (k >= (unsigned long long)(c1 - drawn)) return false;
+        v = uniform(drawn + (int)k);
+        draw();
+        return true;
+    }
+};
+
 // Work item v of a pass whose home cells are shared by `split` wavefronts
 // each: its cell, and its part of the cell's queries [q0, q1) (contiguous
 // parts of equal length; the last ones may be empty).  split <= 1: item v is

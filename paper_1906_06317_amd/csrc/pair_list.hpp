@@ -313,9 +313,12 @@ struct Filler {
     {
         wave_sync();
         if constexpr (NL) {
+            // every block's row starts by one read: lane b holds block b's word
+            unsigned long long sw = 0ull;
+            if (lane < kHitCap / 64) sw = W.starts[lane];
             int before = 0;  // row starts in earlier 64-hit blocks
             for (int e0 = 0; e0 < nh; e0 += kWave) {
-                const unsigned long long bm = uniform64(W.starts[e0 >> 6]);
+                const unsigned long long bm = (unsigned long long)lane_of64((long long)sw, e0 >> 6);
                 const int e = e0 + lane;
                 // starts at hits e0 .. e: those at bits 1 .. lane counted by
                 // the mbcnt of bm >> 1, plus bit 0

@@ -422,3 +422,29 @@ def test_sort_rows_without_distances(ppa):
         for q in range(len(off) - 1):
             a, b = off[q], off[q + 1]
             assert np.array_equal(si[a:b], np.sort(pi[a:b])), f"row {q}"
+
+
+@pytest.mark.parametrize("dim,n,r_max", [(3, 400000, 1.0), (2, 300000, 1.6)])
+def test_drawn_home_cells_cover_every_row(ppa, dim, n, r_max):
+    """Enough home cells that the fill pass draws part of them from its queues
+    (in 2D and 3D, with and without a list): the count pass, which deals its
+    cells, and the fill pass agree on every row, and the histograms agree."""
+    import torch
+    s = workloads.uniform(n, 1.0, seed=930 + dim, dim=dim)
+    box = ppa.Box(s.L, s.tilt, s.dim)
+    pts = torch.as_tensor(s.points).cuda()
+    h, nl = ppa.rdf_counts(box, pts, 64, r_max, neighbor_list=True)
+    alone = ppa.rdf_counts(box, pts, 64, r_max)
+    assert int(h.sum()) == nl.n_pairs and torch.equal(h, ppa.rdf_from_nlist(nl, 64, r_max))
+    # in/out of the list is by the expanded test, alone by the difference: pairs
+    # within the parity band (1e-5 of r_max^2) of the cutoff may differ
+    assert abs(int(alone.sum()) - nl.n_pairs) <= 4e-5 * nl.n_pairs
+    assert torch.equal(alone[:-1], h[:-1])
+    q = nl.query_point_indices().long()
+    d = nl.point_idx.long()
+    assert int((q == d).sum()) == 0
+    # every pair is listed from both sides, and no row holds a neighbour twice
+    key, rev = q * n + d, d * n + q
+    key, rev = key.sort().values, rev.sort().values
+    assert int((key[1:] == key[:-1]).sum()) == 0
+    assert int((key != rev).sum()) <= 8e-5 * nl.n_pairs
