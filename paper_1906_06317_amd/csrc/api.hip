@@ -270,6 +270,18 @@ using namespace ppa;
 
 namespace {
 
+// Cell lists of the points and, when they are separate, of the query points
+// (whose order inside a cell never shows).
+void build_cells(const float* pts, const float* qpts, Workspace& W, const BoxPrep& bp,
+                 const Grid& g, bool ordered, hipStream_t s)
+{
+    launch_build_cells(pts, W.pts, bp, g, ordered, W.status, s);
+    if (qpts)
+        launch_build_cells(qpts, W.qry, bp, g, false, W.status, s);
+    else
+        W.qry = W.pts;
+}
+
 struct QueryCall {
     const ppa_box* box;
     const float* pts;
@@ -335,8 +347,8 @@ int run_pairs(const QueryCall& c)
 
     // n_pairs_dev doubles as the reservation counter of the one-pass mode
     launch_zero(W, g, c.qpts != nullptr, nullptr, 0, s);
-    launch_build_cells(c.pts, W.pts, bp, g, W.status, s);
-    if (c.qpts) launch_build_cells(c.qpts, W.qry, bp, g, W.status, s);
+    // rows list each stencil cell's points by index unless they are sorted later
+    build_cells(c.pts, c.qpts, W, bp, g, c.want_nl && !(c.flags & PPA_SORT_ROWS), s);
 
     PairArgs A{};
     A.cand = W.pts.local;
@@ -480,8 +492,7 @@ int run_knn(const ppa_box* box, const float* pts, int64_t n, const float* qpts, 
     const Grid& g = P.g;
 
     launch_zero(W, g, qpts != nullptr, nullptr, 0, s);  // also clears the deferred counter
-    launch_build_cells(pts, W.pts, bp, g, W.status, s);
-    if (qpts) launch_build_cells(qpts, W.qry, bp, g, W.status, s);
+    build_cells(pts, qpts, W, bp, g, false, s);
 
     KnnArgs A{};
     A.cand = W.pts.local;
@@ -644,8 +655,7 @@ int run_pmft(const ppa_box* box, const float* pts, int64_t n, const float* qpts,
     if (nq == 0) return PPA_OK;
     const Grid& g = P.g;
     launch_zero(W, g, qpts != nullptr, nullptr, 0, s);
-    launch_build_cells(pts, W.pts, bp, g, W.status, s);
-    if (qpts) launch_build_cells(qpts, W.qry, bp, g, W.status, s);
+    build_cells(pts, qpts, W, bp, g, false, s);
 
     PmftArgs A{};
     A.cand = W.pts.local;
@@ -758,8 +768,7 @@ int run_pmft3(const Pmft3Call& c, int32_t exclude_ii, int32_t flags, void* ws, s
     workspace_layout(g, c.n, nq_sep, 0, ws, &W);
     if (c.nq == 0) return PPA_OK;
     launch_zero(W, g, c.qpts != nullptr, nullptr, 0, s);
-    launch_build_cells(c.pts, W.pts, bp, g, W.status, s);
-    if (c.qpts) launch_build_cells(c.qpts, W.qry, bp, g, W.status, s);
+    build_cells(c.pts, c.qpts, W, bp, g, false, s);
 
     Pmft3Args A{};
     A.cand = W.pts.local;
@@ -862,8 +871,7 @@ int run_corr(const ppa_box* box, const float* pts, const float* values, int64_t 
     if (nq == 0) return PPA_OK;
     const Grid& g = P.g;
     launch_zero(W, g, qpts != nullptr, nullptr, 0, s);
-    launch_build_cells(pts, W.pts, bp, g, W.status, s);
-    if (qpts) launch_build_cells(qpts, W.qry, bp, g, W.status, s);
+    build_cells(pts, qpts, W, bp, g, false, s);
 
     A.cand = W.pts.local;
     A.cand_start = W.pts.cell_start;
@@ -957,7 +965,8 @@ int run_smooth(const ppa_box* box, const float* pts, int64_t n, int32_t bins, fl
     if (n == 0) return PPA_OK;
     const Grid& g = P.g;
     launch_zero(W, g, false, nullptr, 0, s);
-    launch_build_cells(pts, W.pts, bp, g, W.status, s);
+    // the adjoint sums each row in list order: ordered, so that it repeats bit for bit
+    build_cells(pts, nullptr, W, bp, g, adjoint, s);
 
     SmoothArgs A{};
     A.cand = W.pts.local;
