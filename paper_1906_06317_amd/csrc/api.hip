@@ -270,18 +270,6 @@ using namespace ppa;
 
 namespace {
 
-// Cell lists of the points and, when they are separate, of the query points
-// (whose order inside a cell never shows).
-void build_cells(const float* pts, const float* qpts, Workspace& W, const BoxPrep& bp,
-                 const Grid& g, bool ordered, hipStream_t s)
-{
-    launch_build_cells(pts, W.pts, bp, g, ordered, W.status, s);
-    if (qpts)
-        launch_build_cells(qpts, W.qry, bp, g, false, W.status, s);
-    else
-        W.qry = W.pts;
-}
-
 struct QueryCall {
     const ppa_box* box;
     const float* pts;
@@ -345,10 +333,8 @@ int run_pairs(const QueryCall& c)
     workspace_layout(g, c.n, nq_sep, lay_flags, c.ws, &W);
     hipStream_t s = c.stream;
 
-    // n_pairs_dev doubles as the reservation counter of the one-pass mode
-    launch_zero(W, g, c.qpts != nullptr, nullptr, 0, s);
     // rows list each stencil cell's points by index unless they are sorted later
-    build_cells(c.pts, c.qpts, W, bp, g, c.want_nl && !(c.flags & PPA_SORT_ROWS), s);
+    launch_build_cells(c.pts, c.qpts, W, bp, g, c.want_nl && !(c.flags & PPA_SORT_ROWS), s);
 
     PairArgs A{};
     A.cand = W.pts.local;
@@ -491,8 +477,7 @@ int run_knn(const ppa_box* box, const float* pts, int64_t n, const float* qpts, 
     Workspace& W = S.W;
     const Grid& g = P.g;
 
-    launch_zero(W, g, qpts != nullptr, nullptr, 0, s);  // also clears the deferred counter
-    build_cells(pts, qpts, W, bp, g, false, s);
+    launch_build_cells(pts, qpts, W, bp, g, false, s);
 
     KnnArgs A{};
     A.cand = W.pts.local;
@@ -654,8 +639,7 @@ int run_pmft(const ppa_box* box, const float* pts, int64_t n, const float* qpts,
     pmft_layout(P, n, nq_sep, ws, &W, &partial, &level2);
     if (nq == 0) return PPA_OK;
     const Grid& g = P.g;
-    launch_zero(W, g, qpts != nullptr, nullptr, 0, s);
-    build_cells(pts, qpts, W, bp, g, false, s);
+    launch_build_cells(pts, qpts, W, bp, g, false, s);
 
     PmftArgs A{};
     A.cand = W.pts.local;
@@ -767,8 +751,7 @@ int run_pmft3(const Pmft3Call& c, int32_t exclude_ii, int32_t flags, void* ws, s
                          need, ws_bytes);
     workspace_layout(g, c.n, nq_sep, 0, ws, &W);
     if (c.nq == 0) return PPA_OK;
-    launch_zero(W, g, c.qpts != nullptr, nullptr, 0, s);
-    build_cells(c.pts, c.qpts, W, bp, g, false, s);
+    launch_build_cells(c.pts, c.qpts, W, bp, g, false, s);
 
     Pmft3Args A{};
     A.cand = W.pts.local;
@@ -870,8 +853,7 @@ int run_corr(const ppa_box* box, const float* pts, const float* values, int64_t 
     corr_layout(P, n, nq_sep, bins, ws, &W, &A);
     if (nq == 0) return PPA_OK;
     const Grid& g = P.g;
-    launch_zero(W, g, qpts != nullptr, nullptr, 0, s);
-    build_cells(pts, qpts, W, bp, g, false, s);
+    launch_build_cells(pts, qpts, W, bp, g, false, s);
 
     A.cand = W.pts.local;
     A.cand_start = W.pts.cell_start;
@@ -964,9 +946,8 @@ int run_smooth(const ppa_box* box, const float* pts, int64_t n, int32_t bins, fl
     smooth_layout(P, n, bins, ws, &W, &partial, &level2, &table);
     if (n == 0) return PPA_OK;
     const Grid& g = P.g;
-    launch_zero(W, g, false, nullptr, 0, s);
     // the adjoint sums each row in list order: ordered, so that it repeats bit for bit
-    build_cells(pts, nullptr, W, bp, g, adjoint, s);
+    launch_build_cells(pts, nullptr, W, bp, g, adjoint, s);
 
     SmoothArgs A{};
     A.cand = W.pts.local;

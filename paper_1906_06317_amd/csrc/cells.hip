@@ -21,7 +21,7 @@ struct ZeroRanges {
     int count;
 };
 
-__global__ void zero_kernel(ZeroRanges z)
+__device__ __forceinline__ void zero_ranges(const ZeroRanges& z)
 {
     for (int r = 0; r < z.count; ++r) {
         unsigned* p = z.ptr[r];
@@ -32,16 +32,14 @@ __global__ void zero_kernel(ZeroRanges z)
     }
 }
 
+__global__ void zero_kernel(ZeroRanges z) { zero_ranges(z); }
+
 constexpr int kAssignRounds = 16;  // grouping rounds; lanes left over take an atomic each
 
-// Cell index and cell-centred local coordinates of point i, in float64;
-// cells of this box are numbered from cell_base.  Writes cell_of[i] and
-// local[i]; returns the cell.
-__device__ __forceinline__ int locate_point(const float* __restrict__ pts, int64_t i,
-                                            const AssignBox& B, int cell_base,
-                                            int* __restrict__ cell_of,
-                                            float4* __restrict__ local,
-                                            unsigned* __restrict__ status)
+// Cell of point i in this box and its cell-centred local coordinates (index
+// bits in w), in float64.
+__device__ __forceinline__ int locate(const float* __restrict__ pts, int64_t i, const AssignBox& B,
+                                      unsigned* __restrict__ status, float4& out)
 {
     double p0 = (double)pts[3 * i];
     double p1 = (double)pts[3 * i + 1];
@@ -69,9 +67,22 @@ __device__ __forceinline__ int locate_point(const float* __restrict__ pts, int64
     const double x = B.M[0][0] * f[0] + B.M[0][1] * f[1] + B.M[0][2] * f[2];
     const double y = B.M[1][1] * f[1] + B.M[1][2] * f[2];
     const double z = B.M[2][2] * f[2];
-    const int cell = cell_base + (c[2] * B.ni[1] + c[1]) * B.ni[0] + c[0];
+    out = make_float4((float)x, (float)y, (float)z, __int_as_float((int)i));
+    return (c[2] * B.ni[1] + c[1]) * B.ni[0] + c[0];
+}
+
+// locate, cells of this box numbered from cell_base; writes cell_of[i] and
+// local[i].
+__device__ __forceinline__ int locate_point(const float* __restrict__ pts, int64_t i,
+                                            const AssignBox& B, int cell_base,
+                                            int* __restrict__ cell_of,
+                                            float4* __restrict__ local,
+                                            unsigned* __restrict__ status)
+{
+    float4 v;
+    const int cell = cell_base + locate(pts, i, B, status, v);
     cell_of[i] = cell;
-    local[i] = make_float4((float)x, (float)y, (float)z, __int_as_float((int)i));
+    local[i] = v;
     return cell;
 }
 
@@ -120,6 +131,143 @@ __global__ void __launch_bounds__(256) assign_kernel(const float* pts, int64_t n
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     assign_point(pts, i, B, 0, cell_of, slot, local, cell_count, status);
+}
+
+// Few cells for the points (kFewCells at most, kFewPerCell points each or
+// more): the counters lie on a handful of cache lines, whose atomics are
+// serialised (50,021 points in 216 cells took 25 us, nearly all of it waiting).
+// A workgroup counts its 1024 points per cell in LDS first and takes its run
+// of every cell's slots with one atomic per cell it met (4.1 us).
+constexpr int kFewCells = 2048;
+constexpr int kFewPerCell = 8;
+constexpr int kFewBlock = 1024;
+
+__global__ void __launch_bounds__(kFewBlock) assign_few_kernel(const float* pts, int64_t n,
+                                                               AssignBox B, int ncells,
+                                                               int* cell_of, int* slot,
+                                                               float4* local, int* cell_count,
+                                                               unsigned* status)
+{
+    __shared__ int s_cnt[kFewCells];
+    for (int c = threadIdx.x; c < ncells; c += kFewBlock) s_cnt[c] = 0;
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * kFewBlock + threadIdx.x;
+    int cell = 0, mine = 0;
+    if (i < n) {
+        cell = locate_point(pts, i, B, 0, cell_of, local, status);
+        mine = atomicAdd(&s_cnt[cell], 1);
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < ncells; c += kFewBlock) {
+        const int k = s_cnt[c];
+        if (k) s_cnt[c] = atomicAdd(&cell_count[c], k);
+    }
+    __syncthreads();
+    if (i < n) slot[i] = s_cnt[cell] + mine;
+}
+
+// A small system's whole cell list in one workgroup: the call's cleared
+// regions, cell of every point, counts and their scan, and the sorted points,
+// all counters and orders in LDS.  The general path's five launches take about
+// 20 us however few the points; this is bound by the vector rate of its one
+// CU.  Ball list at r = 2, density 0.8 (whole call): 1000 points 36.9 -> 28.7 us,
+// 4096 points 41.0 -> 39.9 us; rows sorted by index 52.4 -> 35.5 and 55.8 -> 44.4 us.
+// An ordered list compares every point with its cell's: at 4096 points in 125
+// cells it took as long as the five launches (19.6 us), so past kSmallPairs
+// comparisons (points times the mean run) those are taken.
+constexpr int kSmallPoints = 4096;
+constexpr int64_t kSmallPairs = 1 << 16;
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallPer = kSmallPoints / kSmallBlock;
+constexpr int kSmallCells = 8192;
+
+template <bool ORDERED>
+__global__ void __launch_bounds__(kSmallBlock) small_cells_kernel(const float* pts, int n,
+                                                                  AssignBox B, int ncells,
+                                                                  int* cell_of, float4* out,
+                                                                  int* cell_start,
+                                                                  unsigned* status, ZeroRanges z)
+{
+    extern __shared__ int s_start[];  // [ncells + 1] counts, then starts
+    __shared__ int s_sum[kSmallBlock / kWave];
+    __shared__ int s_id[ORDERED ? kSmallPoints : 1];    // point at a sorted place (arrival order)
+    __shared__ int s_cell[ORDERED ? kSmallPoints : 1];  // its cell
+    __shared__ int s_pos[ORDERED ? kSmallPoints : 1];   // final place of a point
+    const int tid = threadIdx.x;
+    zero_ranges(z);
+    __threadfence();  // the status word is cleared before a point sets it
+    for (int c = tid; c <= ncells; c += kSmallBlock) s_start[c] = 0;
+    __syncthreads();
+    float4 v[kSmallPer];
+    int cell[kSmallPer], mine[kSmallPer];
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k) {
+        const int i = tid + k * kSmallBlock;
+        cell[k] = mine[k] = 0;
+        if (i < n) {
+            cell[k] = locate(pts, i, B, status, v[k]);
+            cell_of[i] = cell[k];
+            mine[k] = atomicAdd(&s_start[cell[k]], 1);
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the counts, a run of consecutive cells per thread
+    const int per = (ncells + kSmallBlock - 1) / kSmallBlock;
+    const int c0 = min(ncells, tid * per), c1 = min(ncells, c0 + per);
+    int sum = 0;
+    for (int c = c0; c < c1; ++c) sum += s_start[c];
+    const int lane = tid & (kWave - 1), wv = tid / kWave;
+    int incl = sum;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int t = __shfl_up(incl, d);
+        if (lane >= d) incl += t;
+    }
+    if (lane == kWave - 1) s_sum[wv] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (int w = 0; w < wv; ++w) run += s_sum[w];
+    for (int c = c0; c < c1; ++c) {
+        const int cnt = s_start[c];
+        s_start[c] = run;
+        cell_start[c] = run;
+        run += cnt;
+    }
+    if (tid == 0) {
+        s_start[ncells] = n;
+        cell_start[ncells] = n;
+    }
+    __syncthreads();
+    if (!ORDERED) {
+#pragma unroll
+        for (int k = 0; k < kSmallPer; ++k)
+            if (tid + k * kSmallBlock < n) out[s_start[cell[k]] + mine[k]] = v[k];
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k) {
+        const int i = tid + k * kSmallBlock;
+        if (i < n) {
+            const int p = s_start[cell[k]] + mine[k];
+            s_id[p] = i;
+            s_cell[p] = cell[k];
+        }
+    }
+    __syncthreads();
+    // ranks by index inside each run; neighbouring lanes share a run, so
+    // their reads are broadcasts
+    for (int p = tid; p < n; p += kSmallBlock) {
+        const int id = s_id[p], b = s_start[s_cell[p]], e = s_start[s_cell[p] + 1];
+        int r = 0;
+        for (int j = b; j < e; ++j) r += s_id[j] < id;
+        s_pos[id] = b + r;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSmallPer; ++k) {
+        const int i = tid + k * kSmallBlock;
+        if (i < n) out[s_pos[i]] = v[k];
+    }
 }
 
 // A batch: every point finds its frame (point_base[f] <= i < point_base[f+1])
@@ -500,8 +648,8 @@ void launch_scan_i64_total(const int* in, int64_t* out, int64_t n, unsigned long
     launch_scan<int64_t>(in, out, n, flags, ticket, total, s);
 }
 
-void launch_zero(Workspace& ws, const Grid& g, bool separate_queries, void* extra,
-                 size_t extra_bytes, hipStream_t s)
+static ZeroRanges cleared(Workspace& ws, const Grid& g, bool separate_queries, bool cells,
+                          void* extra, size_t extra_bytes)
 {
     ZeroRanges z{};
     auto add = [&](void* p, size_t bytes) {
@@ -510,17 +658,26 @@ void launch_zero(Workspace& ws, const Grid& g, bool separate_queries, void* extr
         ++z.count;
     };
     add(ws.status, kHeaderBytes);  // status word, counters and work queues
-    const size_t nf = scan_flag_count(g.ncells);
-    add(ws.pts.cell_count, sizeof(int) * (size_t)g.ncells);
-    add(ws.pts.scan_flags, sizeof(unsigned long long) * nf + 256);
-    if (separate_queries) {
-        add(ws.qry.cell_count, sizeof(int) * (size_t)g.ncells);
-        add(ws.qry.scan_flags, sizeof(unsigned long long) * nf + 256);
+    if (cells) {
+        const size_t nf = scan_flag_count(g.ncells);
+        add(ws.pts.cell_count, sizeof(int) * (size_t)g.ncells);
+        add(ws.pts.scan_flags, sizeof(unsigned long long) * nf + 256);
+        if (separate_queries) {
+            add(ws.qry.cell_count, sizeof(int) * (size_t)g.ncells);
+            add(ws.qry.scan_flags, sizeof(unsigned long long) * nf + 256);
+        }
     }
     if (ws.row_scan_flags)
         add(ws.row_scan_flags, sizeof(unsigned long long) * scan_flag_count(ws.qry.n) + 256);
     if (extra) add(extra, extra_bytes);
-    hipLaunchKernelGGL(zero_kernel, dim3(256), dim3(256), 0, s, z);
+    return z;
+}
+
+void launch_zero(Workspace& ws, const Grid& g, bool separate_queries, void* extra,
+                 size_t extra_bytes, hipStream_t s)
+{
+    hipLaunchKernelGGL(zero_kernel, dim3(256), dim3(256), 0, s,
+                       cleared(ws, g, separate_queries, true, extra, extra_bytes));
 }
 
 // Counting sort of the assigned points into their cells: scan of the cell
@@ -554,8 +711,7 @@ static void finish_cells(CellList& cl, int ncells, bool ordered, hipStream_t s)
     }
 }
 
-void launch_build_cells(const float* pts, CellList& cl, const BoxPrep& b, const Grid& g,
-                        bool ordered, unsigned* status, hipStream_t s)
+static AssignBox assign_box(const BoxPrep& b, const Grid& g)
 {
     AssignBox ab;
     for (int r = 0; r < 3; ++r)
@@ -569,12 +725,54 @@ void launch_build_cells(const float* pts, CellList& cl, const BoxPrep& b, const 
         ab.ni[k] = g.n[k];
     }
     ab.dim = b.dim;
+    return ab;
+}
+
+// The cell list of one point set (counters cleared).
+static void build_general(const float* pts, CellList& cl, const AssignBox& ab, int ncells,
+                          bool ordered, unsigned* status, hipStream_t s)
+{
     const int64_t n = cl.n;
     const unsigned blocks = (unsigned)((n + 255) / 256);
-    if (n > 0)
+    if (n > 0 && ncells <= kFewCells && n >= (int64_t)kFewPerCell * ncells)
+        hipLaunchKernelGGL(assign_few_kernel, dim3((unsigned)((n + kFewBlock - 1) / kFewBlock)),
+                           dim3(kFewBlock), 0, s, pts, n, ab, ncells, cl.cell_of, cl.slot,
+                           cl.local, cl.cell_count, status);
+    else if (n > 0)
         hipLaunchKernelGGL(assign_kernel, dim3(blocks), dim3(256), 0, s, pts, n, ab, cl.cell_of,
                            cl.slot, cl.local, cl.cell_count, status);
-    finish_cells(cl, g.ncells, ordered, s);
+    finish_cells(cl, ncells, ordered, s);
+}
+
+static void build_small(const float* pts, CellList& cl, const AssignBox& ab, int ncells,
+                        bool ordered, unsigned* status, const ZeroRanges& z, hipStream_t s)
+{
+    const size_t lds = sizeof(int) * ((size_t)ncells + 1);
+    const auto k = ordered ? small_cells_kernel<true> : small_cells_kernel<false>;
+    (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)lds);
+    hipLaunchKernelGGL(k, dim3(1), dim3(kSmallBlock), lds, s, pts, (int)cl.n, ab, ncells,
+                       cl.cell_of, cl.local, cl.cell_start, status, z);
+}
+
+void launch_build_cells(const float* pts, const float* qpts, Workspace& W, const BoxPrep& b,
+                        const Grid& g, bool ordered, hipStream_t s)
+{
+    const AssignBox ab = assign_box(b, g);
+    const bool sep = qpts != nullptr;
+    const bool small = W.pts.n <= kSmallPoints && (!sep || W.qry.n <= kSmallPoints) &&
+                       g.ncells <= kSmallCells &&
+                       (!ordered || W.pts.n * W.pts.n <= kSmallPairs * g.ncells);
+    if (small) {
+        build_small(pts, W.pts, ab, g.ncells, ordered, W.status,
+                    cleared(W, g, sep, false, nullptr, 0), s);
+        if (sep) build_small(qpts, W.qry, ab, g.ncells, false, W.status, ZeroRanges{}, s);
+    } else {
+        launch_zero(W, g, sep, nullptr, 0, s);
+        build_general(pts, W.pts, ab, g.ncells, ordered, W.status, s);
+        if (sep) build_general(qpts, W.qry, ab, g.ncells, false, W.status, s);
+    }
+    if (!sep) W.qry = W.pts;
 }
 
 void launch_build_cells_batch(const float* pts, CellList& cl, const FrameInfo* frames,

@@ -131,9 +131,12 @@ int hip_check(hipError_t e, const char* what);
 // Launchers (cells.hip).
 void launch_zero(Workspace& ws, const Grid& g, bool separate_queries, void* extra,
                  size_t extra_bytes, hipStream_t s);
-// ordered: each cell's run by point index (cl.local holds the result either way)
-void launch_build_cells(const float* pts, CellList& cl, const BoxPrep& b, const Grid& g,
-                        bool ordered, unsigned* status, hipStream_t s);
+// Clears a call's counters and builds the cell lists of its points and, when
+// they are separate (qpts not NULL), of its query points; the sorted points
+// are in W.pts.local and W.qry.local afterwards.  ordered: each cell's run of
+// the points by index (the order of separate query points never shows).
+void launch_build_cells(const float* pts, const float* qpts, Workspace& W, const BoxPrep& b,
+                        const Grid& g, bool ordered, hipStream_t s);
 void launch_scan_i64(const int* in, int64_t* out, int64_t n, unsigned long long* flags,
                      int* ticket, hipStream_t s);
 void launch_scan_i64_total(const int* in, int64_t* out, int64_t n, unsigned long long* flags,

@@ -448,3 +448,35 @@ def test_drawn_home_cells_cover_every_row(ppa, dim, n, r_max):
     key, rev = key.sort().values, rev.sort().values
     assert int((key[1:] == key[:-1]).sum()) == 0
     assert int((key != rev).sum()) <= 8e-5 * nl.n_pairs
+
+
+@pytest.mark.parametrize("n,r_max", [(1, 1.0), (65, 1.0), (1023, 2.0), (1025, 2.0), (4095, 1.2),
+                                     (4096, 2.0), (4097, 2.0), (20001, 4.0), (20001, 1.6)])
+@pytest.mark.parametrize("separate", [False, True])
+def test_cell_builds_of_each_size(ppa, n, r_max, separate):
+    """The one-workgroup cell build (up to 4096 points and queries), the build
+    for few cells (20,001 points, r = 4) and the general one, around their
+    limits: rows against the oracle, rows in one order from call to call, the
+    same rows by index with sort_rows, the histogram alone equal to the list's."""
+    import torch
+    s = workloads.uniform(n, 0.8 if n > 100 else 0.05, seed=950 + n, tilt=(0.1, -0.05, 0.1))
+    box = _box(s)
+    q = None
+    if separate:
+        rng = np.random.default_rng(951 + n)
+        q = s.points[rng.permutation(n)[:max(1, n // 3)]] + np.float32(0.01)
+    counts, nl = ppa.rdf_counts(box, s.points, 40, r_max, query_points=q, neighbor_list=True)
+    nq = n if q is None else q.shape[0]
+    rows = range(0, nq, max(1, nq // 400))
+    check_rows(nl, _oracle_rows(s, r_max, list(rows), query_points=q), list(rows), r_max)
+    again = ppa.query_ball(box, s.points, r_max, query_points=q,
+                           exclude_ii=q is None)
+    assert torch.equal(nl.offsets, again.offsets) and torch.equal(nl.point_idx, again.point_idx)
+    by_index = ppa.query_ball(box, s.points, r_max, query_points=q, exclude_ii=q is None,
+                              sort_rows=True)
+    key = nl.query_point_indices().long() * n + nl.point_idx
+    order = key.argsort()
+    assert torch.equal(by_index.point_idx, nl.point_idx[order])
+    assert torch.equal(by_index.dist, nl.dist[order])
+    alone = ppa.rdf_counts(box, s.points, 40, r_max, query_points=q)
+    assert torch.equal(alone[:-1], counts[:-1])
