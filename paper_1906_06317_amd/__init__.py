@@ -189,9 +189,13 @@ def _ptr(t):
 
 
 def _stream(stream=None):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    C = _torch()._C
+    try:  # the raw handle alone: a Stream object costs several microseconds
+        return ctypes.c_void_p(C._cuda_getCurrentRawStream(C._cuda_getDevice()))
+    except AttributeError:
+        return ctypes.c_void_p(_torch().cuda.current_stream().cuda_stream)
 
 
 def _points(points):
@@ -269,7 +273,8 @@ def _estimate_pairs(box: Box, n, nq, r):
 
 
 def _run_pairs(box, points, r_max, query_points, exclude_ii, capacity, with_dist, hist, bins,
-               r_min, want_nl, ws, stream, check, sort_rows=False):
+               r_min, want_nl, ws, stream, check, sort_rows=False, hist_zero=False):
+    # hist_zero: `hist` holds zeros, so a second attempt need not restore it
     torch = _torch()
     pts = _points(points)
     n = pts.shape[0]
@@ -307,7 +312,8 @@ def _run_pairs(box, points, r_max, query_points, exclude_ii, capacity, with_dist
         pidx = torch.empty(max(capacity, 1), dtype=torch.int32, device=dev)
         dist = torch.empty(max(capacity, 1), dtype=torch.float32, device=dev) if with_dist else None
         npairs = torch.zeros(1, dtype=torch.int64, device=dev)
-        h0 = hist.clone() if (hist is not None and attempt == 0) else None
+        if attempt == 0:
+            h0 = None if hist is None or hist_zero else hist.clone()
         if hist is None:
             rc = lib().ppa_query_ball(ctypes.byref(cb), _ptr(pts), n, _ptr(q), nq, float(r_max),
                                       int(bool(exclude_ii)), qflags, wptr, wlen, _ptr(offsets),
@@ -322,8 +328,11 @@ def _run_pairs(box, points, r_max, query_points, exclude_ii, capacity, with_dist
         st = ws.status(stream)
         if st == PPA_ECAPACITY and attempt == 0:
             capacity = int(npairs.item())
+            # the histogram was complete; it is recomputed with the list
             if h0 is not None:
-                hist.copy_(h0)  # the histogram was complete; it is recomputed with the list
+                hist.copy_(h0)
+            elif hist is not None:
+                hist.zero_()
             continue
         if check or st == PPA_ENONFINITE:
             _check(st)
@@ -350,10 +359,11 @@ def rdf_counts(box: Box, points, bins, r_max, r_min=0.0, query_points=None, excl
     With neighbor_list=True the same pass also returns the NeighborList
     (each row ordered by neighbour index with sort_rows=True)."""
     torch = _torch()
-    if counts is None:
+    fresh = counts is None
+    if fresh:
         counts = torch.zeros(int(bins), dtype=torch.int64, device="cuda")
     nl = _run_pairs(box, points, r_max, query_points, exclude_ii, capacity, True, counts, bins,
-                    r_min, neighbor_list, ws, stream, check, sort_rows)
+                    r_min, neighbor_list, ws, stream, check, sort_rows, hist_zero=fresh)
     return (counts, nl) if neighbor_list else counts
 
 
@@ -399,7 +409,9 @@ def query_knn(box: Box, points, k, query_points=None, exclude_ii=None, r_guard=0
                                _stream(stream)))
     if check:
         _check(ws.status(stream))
-    np_ = int(npairs.item())
+    # without r_guard and with at least k other points every row is full
+    full = float(r_guard) == 0.0 and n - 1 >= int(k)
+    np_ = nq * int(k) if full else int(npairs.item())
     return NeighborList(offsets, counts, pidx[:np_], None if dist is None else dist[:np_], np_)
 
 
@@ -960,9 +972,11 @@ class BatchPlan:
         pts = _points(points)
         if pts.shape[0] != self.n:
             raise ValueError("points must hold every frame's rows")
+        hist0 = None
         if hist is None:
             hist = torch.zeros((self.n_frames, self.bins), dtype=torch.int64, device=pts.device)
-        hist0 = hist.clone() if check else None
+        elif check:
+            hist0 = hist.clone()
         o = self._out()
         _check(lib().ppa_batch_run(self._h, _ptr(pts), self.wptr, self.wlen, _ptr(hist), *o,
                                    _stream(stream)))
@@ -973,7 +987,10 @@ class BatchPlan:
                 # reported and run again (the histograms restart from their
                 # values before the call)
                 self._grow(int(self.n_pairs.item()))
-                hist.copy_(hist0)
+                if hist0 is None:
+                    hist.zero_()
+                else:
+                    hist.copy_(hist0)
                 o = self._out()
                 _check(lib().ppa_batch_run(self._h, _ptr(pts), self.wptr, self.wlen, _ptr(hist),
                                            *o, _stream(stream)))

@@ -480,3 +480,49 @@ def test_cell_builds_of_each_size(ppa, n, r_max, separate):
     assert torch.equal(by_index.dist, nl.dist[order])
     alone = ppa.rdf_counts(box, s.points, 40, r_max, query_points=q)
     assert torch.equal(alone[:-1], counts[:-1])
+
+
+def test_status_per_thread_and_stream(ppa):
+    """Statuses read by several threads at once, each on its own stream and
+    workspace, and behind work longer than the polling limit: every call sees
+    its own (one thread's input is not finite)."""
+    import threading
+    import torch
+    s = workloads.uniform(300000, 1.0, seed=990)
+    box = ppa.Box(s.L, s.tilt, s.dim)
+    good = torch.as_tensor(s.points).cuda()
+    bad = good.clone()
+    bad[7, 1] = float("nan")
+    want = ppa.rdf_counts(box, good, 32, 2.0)
+    torch.cuda.synchronize()
+    out = {}
+
+    def work(k):
+        st = torch.cuda.Stream()
+        ws = ppa.Workspace()
+        res = []
+        for rep in range(6):
+            h = torch.zeros(32, dtype=torch.int64, device="cuda")
+            torch.cuda.current_stream().synchronize()
+            try:
+                for _ in range(8 if rep == 5 else 1):  # the last status is behind more work
+                    h.zero_()
+                    torch.cuda.current_stream().synchronize()
+                    ppa.rdf_counts(box, bad if k == 2 else good, 32, 2.0, counts=h, ws=ws,
+                                   stream=st, check=False)
+                    st.synchronize() if rep < 5 else None
+                res.append((ws.status(st), h))
+            except Exception as e:  # noqa: BLE001 (reported below)
+                res.append((repr(e), h))
+        out[k] = res
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for k in range(4):
+        for rep, (rc, h) in enumerate(out[k]):
+            assert rc == (ppa.PPA_ENONFINITE if k == 2 else ppa.PPA_OK), (k, rep, rc)
+            if k != 2 and rep < 5:
+                assert torch.equal(h, want)
