@@ -265,6 +265,22 @@ int pair_split(long long ncells, long long nq)
     return s < 1 ? 1 : (int)s;
 }
 
+// Parts per home cell when the histogram pass splits cells by octants (by
+// quadrants in 2D), or 0 when it does not: where the stencils are on average
+// past the register slots (10 of 64), so that pruning pays, and every octant
+// holds a few queries.  Octants are shared by several wavefronts while there
+// are fewer than about 8192 (6144 are resident; 216 cells, 231 points each: 3456
+// wavefronts 248 us, 5184 167 us, 6912 154 us) and each keeps four queries.
+int octant_split(const Grid& g, int dim, long long n, long long nq)
+{
+    const int kinds = dim == 3 ? 8 : 4;
+    if (g.ncells <= 0 || n * g.nsten <= 640LL * g.ncells || nq < 4LL * kinds * g.ncells) return 0;
+    long long m = 8192 / ((long long)g.ncells * kinds);
+    const long long by_queries = nq / ((long long)g.ncells * kinds * 4);
+    if (m > by_queries) m = by_queries;
+    return kinds * (m < 1 ? 1 : (m > 16 ? 16 : (int)m));
+}
+
 }  // namespace ppa
 
 using namespace ppa;
@@ -351,6 +367,18 @@ int run_pairs(const QueryCall& c)
     A.geom.dot = expanded_test_ok(bp, g, c.r_max) ? 1 : 0;
     A.geom.split = pair_split(g.ncells, c.nq);
     A.geom.queue = W.queue;
+    // a candidate this far (squared) from the bounding box of some queries cannot
+    // hit any: the cutoff, 2e-5 of it for the parity band of the tests (1e-5 of
+    // r^2, expanded or not) and 1e-6 of the coordinates' range for the box test
+    {
+        double ext = c.r_max;
+        for (int k = 0; k < bp.dim; ++k)
+            for (int d = 0; d < 3; ++d) ext += fabs(bp.M[d][k]) / g.n[k];
+        const double r = (double)c.r_max * (1.0 + 2e-5) + 1e-6 * ext;
+        A.geom.r2prune = (float)(r * r);
+    }
+    const int parts = c.want_nl ? 0 : octant_split(g, bp.dim, c.n, c.nq);
+    if (parts) A.geom.split = parts;
     A.offsets = c.offsets;
     A.point_idx = c.point_idx;
     A.dist = c.dist;
@@ -373,7 +401,10 @@ int run_pairs(const QueryCall& c)
                               (unsigned long long*)c.n_pairs_dev, s);
     }
     record(pe.ev[2], s);
-    launch_fill(A, dim, excl, c.want_nl, c.want_hist, s);
+    if (parts)
+        launch_full_cells(A, dim, excl, s);
+    else
+        launch_fill(A, dim, excl, c.want_nl, c.want_hist, s);
     record(pe.ev[3], s);
     if (c.want_nl && (c.flags & PPA_SORT_ROWS))
         launch_sort_rows(c.offsets, c.nq, c.point_idx, c.dist, c.capacity, s);

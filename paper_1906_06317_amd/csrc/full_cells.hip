@@ -1,0 +1,298 @@
+// The histogram of full cells: the RDF without a list where a home cell's
+// stencil holds more candidates than the fill pass keeps in register slots (a
+// cutoff that is large against the points' spacing).
+//
+// One wavefront takes the queries of one octant of a home cell (a quadrant in
+// 2D), or an even share of them.  Points near each other share most of their
+// candidates, and candidates past the cutoff from the bounding box of the
+// wavefront's queries can hit none of them: an octant's box and the cutoff
+// cover about 10.5 of the 27 cells' volume, of which a query's ball is 4.2.
+// The stencil is streamed cell by cell, tested against the box (cutoff and
+// the rounding of the tests, r2prune), and what is left is compacted into an
+// LDS stage, from which all the queries take it four register slots at a
+// time; the hits' r^2 are compacted again and binned 64 at a time.  In or out
+// is decided by the expanded test where the host allows it and by r^2 itself
+// elsewhere, and bins come from the difference of coordinates, as in the fill
+// pass.  Bound by vector issue (the tests about half) and, at few wavefronts,
+// by the latency of the compactions.  50,021 points, r = 6, 231 points a cell,
+// 45 M pairs: 231 us with every query of a cell testing every candidate and
+// binning where it was found, 154 us now.
+#include "pair_common.hpp"
+
+namespace ppa {
+
+namespace {
+
+using namespace pair;
+
+constexpr int kR2Cap = 448;      // r^2 buffered per wavefront
+constexpr int kStageSlots = 3;
+constexpr int kStage = kStageSlots * kWave;
+static_assert(2 * kStage <= kR2Cap - kWave, "two queries' hits fit beside a block that waits");
+
+struct FullLds {
+    float r2[kR2Cap];
+    float4 stage[kStage + kWave];  // the part's queries, then the candidates kept
+    StencilLds st;
+};
+
+struct FullOut {
+    unsigned long long* hist;
+    int bins;
+    float r_min, inv_dr;
+};
+
+struct FullBins {
+    FullLds& W;
+    const FullOut O;
+    unsigned* hist;  // in LDS, or NULL: straight into O.hist
+    int lane;
+    int nh;          // r^2 waiting
+
+    __device__ __forceinline__ void bin(float r)
+    {
+        const float t = (r - O.r_min) * O.inv_dr;
+        if (t >= 0.f && t < (float)O.bins) {
+            const int b = min((int)t, O.bins - 1);
+            if (hist)
+                atomicAdd(&hist[b], 1u);
+            else
+                atomicAdd(&O.hist[b], 1ull);
+        }
+    }
+    // Bins whole blocks of 64 (or with `all` everything); the rest moves up.
+    __device__ __forceinline__ void drain(bool all)
+    {
+        wave_sync();
+        int e0 = 0;
+        for (; e0 + 4 * kWave <= nh; e0 += 4 * kWave) {  // four reads in flight
+            float r2[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) r2[u] = W.r2[e0 + u * kWave + lane];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) bin(fast_sqrt(r2[u]));
+        }
+        for (; e0 + kWave <= nh; e0 += kWave) bin(fast_sqrt(W.r2[e0 + lane]));
+        float rest = 0.f;
+        if (lane < nh - e0) rest = W.r2[e0 + lane];
+        if (all) {
+            if (lane < nh - e0) bin(fast_sqrt(rest));
+            nh = 0;
+        } else {
+            wave_sync();
+            if (lane < nh - e0) W.r2[lane] = rest;
+            nh -= e0;
+        }
+        wave_sync();
+    }
+    // Hits of query a, and with TWO of b, against the first `count` candidates.
+    template <int DIM, int EXCL, bool DOT, bool TWO>
+    __device__ __forceinline__ void hits(const Slots<DIM, kStageSlots>& c, const Query& qa,
+                                         const Query& qb, float r2max, int count)
+    {
+        if (nh + (TWO ? 2 : 1) * count > kR2Cap) drain(false);
+#pragma unroll
+        for (int s = 0; s < kStageSlots; ++s) {
+            if (s * kWave >= count) break;  // uniform
+            const float ra = dist2<DIM>(c.x[s] - qa.x, c.y[s] - qa.y, c.z[s] - qa.z);
+            bool ha = DOT ? c.template hit<true>(s, qa, r2max) : ra < r2max;
+            if (EXCL == 2) ha = ha && c.id[s] != qa.id;
+            const unsigned long long ma = __ballot(ha);
+            if (TWO) {
+                const float rb = dist2<DIM>(c.x[s] - qb.x, c.y[s] - qb.y, c.z[s] - qb.z);
+                bool hb = DOT ? c.template hit<true>(s, qb, r2max) : rb < r2max;
+                if (EXCL == 2) hb = hb && c.id[s] != qb.id;
+                const unsigned long long mb = __ballot(hb);
+                const int nb = nh + __popcll(ma);
+                if (ha) W.r2[nh + (int)lane_prefix(ma)] = ra;
+                if (hb) W.r2[nb + (int)lane_prefix(mb)] = rb;
+                nh = nb + __popcll(mb);
+            } else {
+                if (ha) W.r2[nh + (int)lane_prefix(ma)] = ra;
+                nh += __popcll(ma);
+            }
+        }
+    }
+};
+
+// Every query of the chunk against the first `count` staged candidates.
+template <int DIM, int EXCL, bool DOT>
+__device__ __forceinline__ void run_stage(FullBins& F, const QueryChunk& Q, float r2max, int count)
+{
+    wave_sync();
+    const int lane = F.lane;
+    Slots<DIM, kStageSlots> c;
+#pragma unroll
+    for (int s = 0; s < kStageSlots; ++s) {
+        const int e = s * kWave + lane;
+        c.x[s] = c.y[s] = c.z[s] = kFar;
+        c.id[s] = -1;
+        if (e < count) {
+            const float4 v = F.W.stage[e];
+            c.x[s] = v.x;
+            c.y[s] = v.y;
+            c.z[s] = DIM == 3 ? v.z : 0.f;
+            c.id[s] = __float_as_int(v.w);
+        }
+        c.cc[s] = dist2<DIM>(c.x[s], c.y[s], c.z[s]);
+    }
+    int t = 0;
+    for (; t + 1 < Q.n; t += 2)
+        F.template hits<DIM, EXCL, DOT, true>(c, Q.template get<DIM>(t, r2max),
+                                              Q.template get<DIM>(t + 1, r2max), r2max, count);
+    if (t < Q.n) {
+        const Query q = Q.template get<DIM>(t, r2max);
+        F.template hits<DIM, EXCL, DOT, false>(c, q, q, r2max, count);
+    }
+}
+
+// Gathers the part's queries first .. first + 63 into the stage: those of the
+// home cell's queries [q0, q1) in octant oct, every step-th from the sub-th on.
+// Returns how many the part has in all, less `first`.
+template <int DIM>
+__device__ __forceinline__ int gather_part(const PairIn& in, float4* stage, int q0, int q1, int oct,
+                                           int sub, int step, int first, int lane)
+{
+    wave_sync();
+    int seen = 0, taken = 0;  // in the octant, and in the part, so far
+    for (int b = q0; b < q1; b += kWave) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (b + lane < q1) v = in.qs[b + lane];
+        const int o =
+            (v.x >= 0.f ? 1 : 0) | (v.y >= 0.f ? 2 : 0) | (DIM == 3 && v.z >= 0.f ? 4 : 0);
+        const bool mine = b + lane < q1 && o == oct;
+        const unsigned long long m = __ballot(mine);
+        const bool part = mine && (seen + (int)lane_prefix(m)) % step == sub;
+        const unsigned long long mp = __ballot(part);
+        const int at = taken + (int)lane_prefix(mp) - first;
+        if (part && at >= 0 && at < kWave) stage[at] = v;
+        seen += __popcll(m);
+        taken += __popcll(mp);
+    }
+    wave_sync();
+    return taken - first;
+}
+
+// EXCL: 0 keep j == i, 1 points query themselves (each finds its own entry, at
+// r = 0, which is taken out of bin 0 at the end), 2 separate query points
+// (drop j == i by index).
+template <int DIM, int EXCL, bool DOT>
+__global__ void __launch_bounds__(kBlock, 6) full_cells_kernel(const PairIn in, const PairGeom G,
+                                                               const FullOut O)
+{
+    extern __shared__ unsigned s_hist[];
+    __shared__ float4 s_off[27];
+    __shared__ FullLds s_w[kWavesPerBlock];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = uniform(threadIdx.x / kWave);
+    FullLds& W = s_w[wv];
+    const bool lds_hist = O.bins <= kMaxLdsBins;
+    if (threadIdx.x < 27)
+        s_off[threadIdx.x] = make_float4(G.off[threadIdx.x][0], G.off[threadIdx.x][1],
+                                         G.off[threadIdx.x][2], 0.f);
+    if (lds_hist)
+        for (int b = threadIdx.x; b < O.bins; b += kBlock) s_hist[b] = 0u;
+    __syncthreads();
+    FullBins F{W, O, lds_hist ? s_hist : nullptr, lane, 0};
+    int selfs = 0;
+    const float r2max = G.r2max;
+    constexpr int kKinds = DIM == 3 ? 8 : 4;
+    int t0, t1, stride;
+    wave_tiles_interleaved<kWavesPerBlock>(G.ncells * G.split, wv, t0, t1, stride);
+    for (int item = t0; item < t1; item += stride) {
+        const int tile = uniform(item / G.split), p = item - tile * G.split;
+        const int q0 = in.q_start[tile], q1 = in.q_start[tile + 1];
+        if (q0 == q1) continue;
+        stencil<DIM>(in, G, tile, lane, W.st);
+        for (int first = 0;; first += kWave) {
+            QueryChunk Q;
+            Q.n = min(kWave, gather_part<DIM>(in, W.stage, q0, q1, p % kKinds, p / kKinds,
+                                              G.split / kKinds, first, lane));
+            if (Q.n <= 0) break;
+            selfs += Q.n;
+            Q.q = W.stage[lane < Q.n ? lane : 0];
+            wave_sync();
+            // bounding box of the queries
+            const float lx = wave_min(Q.q.x), hx = wave_max(Q.q.x);
+            const float ly = wave_min(Q.q.y), hy = wave_max(Q.q.y);
+            const float lz = DIM == 3 ? wave_min(Q.q.z) : 0.f;
+            const float hz = DIM == 3 ? wave_max(Q.q.z) : 0.f;
+            int ns = 0;  // candidates staged
+            for (int j = 0; j < G.nsten; ++j) {
+                const int k0 = uniform(W.st.pre[j]), k1 = uniform(W.st.pre[j + 1]);
+                const float4 o = s_off[j];
+                const int base = uniform(W.st.base[j]);
+                for (int k = k0; k < k1; k += kWave) {
+                    float4 v = make_float4(kFar, kFar, kFar, 0.f);
+                    if (k + lane < k1) {
+                        v = in.cand[base + k + lane];
+                        v.x += o.x;
+                        v.y += o.y;
+                        v.z = DIM == 3 ? v.z + o.z : 0.f;
+                    }
+                    const float dx = fmaxf(fmaxf(v.x - hx, lx - v.x), 0.f);
+                    const float dy = fmaxf(fmaxf(v.y - hy, ly - v.y), 0.f);
+                    const float dz = DIM == 3 ? fmaxf(fmaxf(v.z - hz, lz - v.z), 0.f) : 0.f;
+                    const bool keep = dist2<DIM>(dx, dy, dz) < G.r2prune;
+                    const unsigned long long m = __ballot(keep);
+                    if (keep) W.stage[ns + (int)lane_prefix(m)] = v;
+                    ns += __popcll(m);
+                    if (ns >= kStage) {
+                        run_stage<DIM, EXCL, DOT>(F, Q, r2max, kStage);
+                        wave_sync();
+                        float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+                        ns -= kStage;
+                        if (lane < ns) w = W.stage[kStage + lane];
+                        wave_sync();
+                        if (lane < ns) W.stage[lane] = w;
+                        wave_sync();
+                    }
+                }
+            }
+            if (ns > 0) run_stage<DIM, EXCL, DOT>(F, Q, r2max, ns);
+        }
+    }
+    F.drain(true);
+    if (EXCL == 1 && selfs > 0 && O.r_min <= 0.f && lane == 0) {
+        if (lds_hist)
+            atomicSub(&s_hist[0], (unsigned)selfs);
+        else
+            atomicAdd(&O.hist[0], (unsigned long long)(-(long long)selfs));
+    }
+    __syncthreads();
+    if (lds_hist)
+        for (int b = threadIdx.x; b < O.bins; b += kBlock) {
+            const unsigned v = s_hist[b];
+            if (v) atomicAdd(&O.hist[b], (unsigned long long)v);
+        }
+}
+
+template <int DIM, int EXCL, bool DOT>
+void launch_full_t(const PairIn& in, const PairGeom& g, const FullOut& o, hipStream_t s)
+{
+    const size_t lds = o.bins <= kMaxLdsBins ? sizeof(unsigned) * (size_t)o.bins : 0;
+    const auto k = full_cells_kernel<DIM, EXCL, DOT>;
+    const int blocks = resident_blocks(k, lds, (long long)g.ncells * g.split);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), lds, s, in, g, o);
+}
+
+}  // namespace
+
+void launch_full_cells(const PairArgs& a, int dim, int excl, hipStream_t s)
+{
+    const PairIn in{a.cand, a.cand_start, a.qsorted, a.q_start};
+    const FullOut o{a.hist, a.bins, a.r_min, a.inv_dr};
+#define PPA_FULL(D, E)                                         \
+    do {                                                       \
+        if (a.geom.dot) launch_full_t<D, E, true>(in, a.geom, o, s); \
+        else launch_full_t<D, E, false>(in, a.geom, o, s);     \
+    } while (0)
+    if (dim == 3) {
+        if (excl == 1) PPA_FULL(3, 1); else if (excl == 2) PPA_FULL(3, 2); else PPA_FULL(3, 0);
+    } else {
+        if (excl == 1) PPA_FULL(2, 1); else if (excl == 2) PPA_FULL(2, 2); else PPA_FULL(2, 0);
+    }
+#undef PPA_FULL
+}
+
+}  // namespace ppa

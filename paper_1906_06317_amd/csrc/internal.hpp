@@ -15,6 +15,15 @@ constexpr int kMaxSlots = 12;           // candidate slots a wave keeps in regis
 constexpr int kCandCap = kMaxSlots * kWave;
 constexpr int kMaxLdsBins = 4096;       // histograms up to this size live in LDS
 
+// 1 / sqrt(x) in float64 from the hardware's approximation (about 2^-23) by one
+// cubic step: relative error about 1e-16.
+__device__ __forceinline__ double inv_sqrt(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y, e * fma(e, 0.375, 0.5), y);
+}
+
 // Device status bits (the status word in the workspace).
 constexpr unsigned kStatusNonFinite = 1u;
 constexpr unsigned kStatusCapacity = 2u;
@@ -153,6 +162,7 @@ void launch_build_cells_batch(const float* pts, CellList& cl, const FrameInfo* f
 bool expanded_test_ok(const BoxPrep& bp, const Grid& g, double r);
 int check_cutoff(const BoxPrep& bp, double r);
 int pair_split(long long ncells, long long nq);
+int octant_split(const Grid& g, int dim, long long n, long long nq);
 
 // Geometry of a pair query (pairs.hip).
 struct PairGeom {
@@ -164,6 +174,8 @@ struct PairGeom {
     float r2max;
     int dot;             // 1: expanded in/out test (its error bound passed on the host)
     int split;           // ball query: wavefronts sharing a home cell's queries (0, 1: one)
+    float r2prune;       // full cells: squared distance from some queries' bounding box past
+                         // which a candidate can hit none (cutoff and the tests' rounding)
     int dealt;           // fill pass: rounds of cells dealt in turn (set by its launch)
     unsigned long long* queue;  // zeroed work-queue counters (fill pass)
 };
@@ -215,6 +227,9 @@ int device_cus();
 
 void launch_count(const PairArgs& a, int dim, int excl, hipStream_t s);
 void launch_fill(const PairArgs& a, int dim, int excl, bool nl, bool hist, hipStream_t s);
+// The histogram alone over cells past the register slots; geom.split parts a
+// cell (octant_split).
+void launch_full_cells(const PairArgs& a, int dim, int excl, hipStream_t s);
 void launch_fill_2d(const PairArgs& a, int excl, bool nl, bool hist, hipStream_t s);
 void launch_fill_3d(const PairArgs& a, int excl, bool nl, bool hist, hipStream_t s);
 // Orders every complete row of a CSR list by neighbour index (distances follow).

@@ -69,6 +69,27 @@ __device__ __forceinline__ int wave_incl_scan(int x)
     return x;
 }
 
+// Minimum and maximum over the wavefront, by the same steps (every lane's value
+// valid; the result is uniform).
+template <bool MAX>
+__device__ __forceinline__ float wave_extreme(float v)
+{
+    int x = __float_as_int(v);
+    auto join = [](int a, int b) {
+        const float p = __int_as_float(a), q = __int_as_float(b);
+        return __float_as_int(MAX ? fmaxf(p, q) : fminf(p, q));
+    };
+    x = join(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xF, 0xF, false));  // row_shr:1
+    x = join(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xF, 0xF, false));  // row_shr:2
+    x = join(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xF, 0xF, false));  // row_shr:4
+    x = join(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xF, 0xF, false));  // row_shr:8
+    x = join(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    x = join(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return __int_as_float(__builtin_amdgcn_readlane(x, kWave - 1));
+}
+__device__ __forceinline__ float wave_min(float v) { return wave_extreme<false>(v); }
+__device__ __forceinline__ float wave_max(float v) { return wave_extreme<true>(v); }
+
 // x + x of lane l ^ 16 (one permlane16 swap), and of lane l ^ 32.
 __device__ __forceinline__ int pair_sum16(int x)
 {

@@ -213,15 +213,6 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// 1 / sqrt(x) in float64 from the hardware's approximation (about 2^-23) by one
-// cubic step: relative error about 1e-16.
-__device__ __forceinline__ double inv_sqrt(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
-    return fma(y, e * fma(e, 0.375, 0.5), y);
-}
-
 // Nodes of the table of -2 A(r): node i at r = i w, w = sigma / 16.  Row i
 // holds the Taylor coefficients in (r - i w) / sigma up to the third: the
 // remainder over half a node, (1/32)^4 / 24 times the fifth Hermite function

@@ -526,3 +526,37 @@ def test_status_per_thread_and_stream(ppa):
             assert rc == (ppa.PPA_ENONFINITE if k == 2 else ppa.PPA_OK), (k, rep, rc)
             if k != 2 and rep < 5:
                 assert torch.equal(h, want)
+
+
+@pytest.mark.parametrize("dim,n,r_max,tilt", [
+    (3, 6000, 4.0, 0.3),     # octants, several wavefronts each
+    (3, 60000, 3.5, 0.0),    # octants, one wavefront each
+    (2, 30000, 9.0, 0.2),    # quadrants
+    (3, 30000, 2.6, 0.0),    # cells around the register slots: tiles and streams
+])
+@pytest.mark.parametrize("r_min,separate", [(0.0, False), (0.7, False), (0.0, True)])
+def test_histogram_of_full_cells(ppa, dim, n, r_max, tilt, r_min, separate):
+    """The histogram alone over cells past the register slots (octant parts,
+    pruned and staged candidates) against the histogram binned with the list;
+    a dense blob puts more than 64 queries in a part."""
+    import torch
+    s = workloads.uniform(n, 1.2, seed=960 + n, dim=dim, tilt=(tilt, 0.0, 0.0))
+    rng = np.random.default_rng(961 + n)
+    blob = rng.normal(0.0, 0.4, size=(1500, 3)).astype(np.float32)
+    pts = s.points.copy()
+    pts[:1500, :dim] = blob[:, :dim] + np.float32(0.3)
+    pts[5] = pts[4]  # coincident points are neighbours at r = 0
+    box = _box(s)
+    q = None
+    if separate:
+        q = pts[rng.permutation(n)[:n // 2]] + np.float32(0.013)
+        q[:, dim:] = 0
+    alone = ppa.rdf_counts(box, pts, 50, r_max, r_min, query_points=q)
+    both, nl = ppa.rdf_counts(box, pts, 50, r_max, r_min, query_points=q, neighbor_list=True)
+    assert torch.equal(alone[:-1], both[:-1])
+    # the last bin: pairs in the parity band of the cutoff may be decided either way
+    assert abs(int(alone[-1]) - int(both[-1])) <= 2 + 4e-5 * nl.n_pairs
+    excl = ppa.rdf_counts(box, pts, 50, r_max, r_min, query_points=q, exclude_ii=False)
+    own = 0 if r_min > 0.0 else (int(excl[0]) - int(alone[0]))
+    assert own == (0 if r_min > 0.0 or separate else n)
+    assert torch.equal(excl[1:], alone[1:])
