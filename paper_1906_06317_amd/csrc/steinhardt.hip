@@ -10,12 +10,17 @@
 // comes from the recurrences of the normalised associated Legendre
 // functions: the sectoral term times e^{i m p} is c_m ((x + i y) / r)^m,
 // advanced from m - 1 by one complex product, and P_l^m / P_m^m follows the
-// upward recurrence in l (one square root and one division per bond); with
+// upward recurrence in l, their constant factors multiplied in once per row
+// (one reciprocal square root per bond); with
 // q_{l,-m} = (-1)^m conj(q_lm) only m >= 0 is accumulated.  The kernel is
 // instantiated per l, so the m loops and the recurrence coefficients are
-// compile-time constants and q_lm stays in registers; for W each lane
-// stages its q_lm in LDS for the double loop over (m1, m2).  The Wigner 3j
-// symbols come from a setup kernel (Racah formula) into the workspace.
+// compile-time constants and q_lm stays in registers, also for W at even l,
+// where symmetry leaves one term per class of (m1, m2, m3); at odd l (W is 0 up
+// to rounding) each lane stages its q_lm in LDS for the full double loop.  The
+// Wigner 3j symbols come from a setup kernel (Racah formula) into the
+// workspace.  Bound by float64 vector issue.  256,000 rows of 12 bonds, Q6 and
+// W6: 61.5 us with a division and factors in every step and the full 3j sum, 23.3 us
+// now.
 #include "internal.hpp"
 
 namespace ppa {
@@ -71,6 +76,35 @@ __device__ __forceinline__ double2 q_of(const double2* q, int m)
     return (m & 1) ? make_double2(-v.x, v.y) : make_double2(v.x, -v.y);
 }
 
+// Constants of the recurrences, folded at compile time.  With a_l =
+// sqrt((4 l^2 - 1) / (l^2 - m^2)) and b_l = sqrt(((l-1)^2 - m^2) / (4 (l-1)^2 - 1)),
+// P_l^m = a_l (x P_{l-1}^m - b_l P_{l-2}^m); divided by its leading factor,
+// p_l = x p_{l-1} - (b_l / a_{l-1}) p_{l-2}.
+// As 1 / a_{l-1} = b_l, that ratio is b_l^2.
+constexpr double step_ratio(int l, int m)
+{
+    return ((double)(l - 1) * (l - 1) - (double)m * m) / (4.0 * (l - 1) * (l - 1) - 1.0);
+}
+// The factors left out of q_lm's terms: the sectoral constant c_m (with the
+// Condon-Shortley phase) times the product of a_l for l = m + 1 .. L.
+template <int L>
+struct SectorScale {
+    double v[L + 1];
+
+    constexpr SectorScale() : v()
+    {
+        for (int m = 0; m <= L; ++m) {
+            double sq = 1.0;
+            for (int k = 1; k <= m; ++k) sq *= (2.0 * k + 1.0) / (2.0 * k);
+            for (int l = m + 1; l <= L; ++l)
+                sq *= (4.0 * l * l - 1.0) / ((double)l * l - (double)m * m);
+            double y = sq;  // its square root, by Newton's iteration
+            for (int k = 0; k < 64; ++k) y = 0.5 * (y + sq / y);
+            v[m] = (m & 1 ? -1.0 : 1.0) * kInvSqrt4Pi * y;
+        }
+    }
+};
+
 // Five wavefronts per SIMD for l <= 6 (96 VGPRs: Q6 with W6 on the k = 12
 // list of the 2^20-point FCC 0.217 -> 0.203 ms); larger l keep their
 // registers (l = 8 at five wavefronts spills; l = 12 bounded to four
@@ -91,23 +125,36 @@ __global__ void __launch_bounds__(kStBlock, (L <= 6 ? 5 : 1)) steinhardt_kernel(
     const float* qp = a.qpts + 3 * i;
     const double qx = qp[0], qy = qp[1], qz = a.dim == 3 ? (double)qp[2] : 0.0;
     int nb = 0;
+    // a bond's index and position are read while the bond before is worked (an
+    // index out of range reads point 0 and is skipped)
+    int jn = 0;
+    float pn[3] = {0.f, 0.f, 0.f};
+    auto fetch = [&](long long e) {
+        jn = a.idx[e];
+        const float* pp = a.pts + 3 * (jn < 0 || (long long)jn >= a.n ? 0LL : (long long)jn);
+        pn[0] = pp[0];
+        pn[1] = pp[1];
+        pn[2] = pp[2];
+    };
+    if (e0 < e1 && a.n > 0) fetch(e0);
     for (long long e = e0; e < e1; ++e) {
-        const int j = a.idx[e];
+        const int j = jn;
+        double d[3] = {(double)pn[0] - qx, (double)pn[1] - qy,
+                       a.dim == 3 ? (double)pn[2] - qz : 0.0};
+        if (e + 1 < e1 && a.n > 0) fetch(e + 1);
         if (j < 0 || (long long)j >= a.n) {
             atomicOr(a.status, kStatusBadList);
             continue;
         }
-        const float* pp = a.pts + 3 * (long long)j;
-        double d[3] = {(double)pp[0] - qx, (double)pp[1] - qy,
-                       a.dim == 3 ? (double)pp[2] - qz : 0.0};
         // minimum image: fractional displacement rounded to the nearest image
-        double s[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            s[k] = rint(a.minv[k][0] * d[0] + a.minv[k][1] * d[1] + a.minv[k][2] * d[2]);
-        if (a.dim != 3) s[2] = 0.0;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) d[k] -= a.m[k][0] * s[0] + a.m[k][1] * s[1] + a.m[k][2] * s[2];
+        // (box matrix and inverse are upper triangular)
+        const double s2i = a.dim == 3 ? rint(a.minv[2][2] * d[2]) : 0.0;
+        const double s1i = rint(fma(a.minv[1][1], d[1], a.minv[1][2] * d[2]));
+        const double s0i =
+            rint(fma(a.minv[0][0], d[0], fma(a.minv[0][1], d[1], a.minv[0][2] * d[2])));
+        d[0] -= fma(a.m[0][0], s0i, fma(a.m[0][1], s1i, a.m[0][2] * s2i));
+        d[1] -= fma(a.m[1][1], s1i, a.m[1][2] * s2i);
+        d[2] -= a.m[2][2] * s2i;
         const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
         if (!isfinite(r2)) {
             atomicOr(a.status, kStatusNonFinite);
@@ -115,52 +162,67 @@ __global__ void __launch_bounds__(kStBlock, (L <= 6 ? 5 : 1)) steinhardt_kernel(
         }
         if (r2 == 0.0) continue;
         ++nb;
-        const double inv_r = 1.0 / sqrt(r2);
+        const double inv_r = inv_sqrt(r2);
         const double x = d[2] * inv_r;                     // cos(theta)
         const double ur = d[0] * inv_r, ui = d[1] * inv_r; // sin(theta) e^{i phi}
-        // sectoral term times e^{i m phi}: c_m (sin(theta) e^{i phi})^m, with the
-        // normalised P_m^m = c_m sin^m(theta) (Condon-Shortley phase)
-        double cr = kInvSqrt4Pi, ci = 0.0;
+        // (sin(theta) e^{i phi})^m times P_L^m / P_m^m by the upward recurrence in
+        // l, both without their constant factors (SectorScale): each step of
+        // the recurrence is then one product and one multiply-add
+        double cr = 1.0, ci = 0.0;
 #pragma unroll
         for (int m = 0; m <= L; ++m) {
             if (m > 0) {
-                const double f = -sqrt((2.0 * m + 1.0) / (2.0 * m));
-                const double t = cr * ur - ci * ui;
-                ci = f * (cr * ui + ci * ur);
-                cr = f * t;
+                const double t = fma(cr, ur, -(ci * ui));
+                ci = fma(cr, ui, ci * ur);
+                cr = t;
             }
-            // P_L^m / P_m^m by the upward recurrence in l (linear in P_m^m)
-            double ratio = 1.0;
-            if (L > m) {
-                double p0 = 1.0;
-                double p1 = sqrt(2.0 * m + 3.0) * x;
+            double p0 = 1.0, p1 = L > m ? x : 1.0;
 #pragma unroll
-                for (int l = m + 2; l <= L; ++l) {
-                    const double al = sqrt((4.0 * l * l - 1.0) / ((double)l * l - (double)m * m));
-                    const double bl = sqrt(((double)(l - 1) * (l - 1) - (double)m * m) /
-                                           (4.0 * (l - 1) * (l - 1) - 1.0));
-                    const double p2 = al * (x * p1 - bl * p0);
-                    p0 = p1;
-                    p1 = p2;
-                }
-                ratio = p1;
+            for (int l = m + 2; l <= L; ++l) {
+                const double p2 = fma(x, p1, -(step_ratio(l, m) * p0));
+                p0 = p1;
+                p1 = p2;
             }
-            re[m] += ratio * cr;
-            im[m] += ratio * ci;
+            re[m] = fma(p1, cr, re[m]);
+            im[m] = fma(p1, ci, im[m]);
         }
+    }
+    constexpr SectorScale<L> scale;
+#pragma unroll
+    for (int m = 0; m <= L; ++m) {
+        re[m] *= scale.v[m];
+        im[m] *= scale.v[m];
     }
     double s2 = re[0] * re[0] + im[0] * im[0];
 #pragma unroll
     for (int m = 1; m <= L; ++m) s2 += 2.0 * (re[m] * re[m] + im[m] * im[m]);
     a.ql[i] = nb > 0 ? sqrt(4.0 * M_PI / (2.0 * L + 1.0) * s2) / nb : 0.0;
-    if (a.wl) {
+    if (!a.wl) return;
+    double w = 0.0;
+    constexpr int W = 2 * L + 1;
+    if constexpr (L % 2 == 0) {
+        // l even: the symbol does not change under permutations or when all m
+        // change sign, and q_{-m} is (-1)^m conj(q_m), so a triple's terms are all
+        // equal and only m1 >= m2 >= 0, m3 = -(m1 + m2) are formed, with their
+        // number of occurrences: (L/2 + 1)^2 terms from registers (16 at l = 6)
+        // instead of 3 l (l + 1) + 1 (127)
+#pragma unroll
+        for (int m2 = 0; 2 * m2 <= L; ++m2)
+#pragma unroll
+            for (int m1 = m2; m1 + m2 <= L; ++m1) {
+                const int m = m1 + m2;
+                const double times = m1 == 0 ? 1.0 : (m2 == 0 ? 6.0 : (m1 == m2 ? 6.0 : 12.0));
+                const double pr = fma(re[m1], re[m2], -(im[m1] * im[m2]));
+                const double pi = fma(re[m1], im[m2], im[m1] * re[m2]);
+                const double t = fma(pr, re[m], pi * im[m]);
+                w = fma(a.w3j[(m1 + L) * W + (m2 + L)] * (m & 1 ? -times : times), t, w);
+            }
+    } else {
         // the lane's q_lm (m >= 0) in LDS, then the 3j sum over m1 + m2 + m3 = 0
         extern __shared__ double2 s_q[];
         double2* q = s_q + threadIdx.x * (L + 1);
 #pragma unroll
         for (int m = 0; m <= L; ++m) q[m] = make_double2(re[m], im[m]);
-        constexpr int W = 2 * L + 1;
-        double w = 0.0;
         for (int m1 = -L; m1 <= L; ++m1) {
             const double2 a1 = q_of(q, m1);
             const int lo = m1 < 0 ? -L - m1 : -L, hi = m1 < 0 ? L : L - m1;
@@ -171,15 +233,15 @@ __global__ void __launch_bounds__(kStBlock, (L <= 6 ? 5 : 1)) steinhardt_kernel(
                 w += a.w3j[(m1 + L) * W + (m2 + L)] * (pr * a3.x - pi * a3.y);
             }
         }
-        a.wl[i] = (nb > 0 && s2 > 0.0) ? w / (s2 * sqrt(s2)) : 0.0;
     }
+    a.wl[i] = (nb > 0 && s2 > 0.0) ? w / (s2 * sqrt(s2)) : 0.0;
 }
 
 template <int L>
 void launch_l(const SteinArgs& a, hipStream_t s)
 {
     const int blocks = (int)((a.nq + kStBlock - 1) / kStBlock);
-    const size_t lds = a.wl ? sizeof(double2) * kStBlock * (L + 1) : 0;
+    const size_t lds = a.wl && L % 2 ? sizeof(double2) * kStBlock * (L + 1) : 0;
     hipLaunchKernelGGL(steinhardt_kernel<L>, dim3(blocks), dim3(kStBlock), lds, s, a);
 }
 
