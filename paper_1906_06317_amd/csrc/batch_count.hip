@@ -18,7 +18,8 @@ __global__ void __launch_bounds__(WPB * kWave, 5) count_batch_kernel(
     StencilLds& S = s_st[wv];
     float4* off = s_off[wv];
     RunQueue R;
-    R.start(B, B.queue, WPB, lane);
+    R.start(B, WPB, wv);
+    const FrameSearch frames(B, lane);
     int f = -1, cur = 0, next = -1;
     GeomView V;
     int t, te;
@@ -27,10 +28,10 @@ __global__ void __launch_bounds__(WPB * kWave, 5) count_batch_kernel(
             const CellPart P = cell_part(in, v, B.split);
             if (P.q0 == P.q1) continue;
             if (P.tile < cur || P.tile >= next) {
-                f = frame_of(B, P.tile, lane);
-                V = load_frame(B, f, off, lane);
+                f = frames.find(B, P.tile, lane);
                 cur = B.cell_base[f];
                 next = B.cell_base[f + 1];
+                V = load_frame(B, f, off, lane);
             }
             const int C = stencil<DIM>(in, V, P.tile, lane, S);
             count_cell<DIM, EXCL>(in, V, S, off, C, P.q0, P.q1, lane, s_q[wv], counts);

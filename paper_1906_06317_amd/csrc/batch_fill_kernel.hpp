@@ -23,6 +23,14 @@ __device__ __forceinline__ void merge_wave_hist(unsigned* h, unsigned long long*
     wave_sync();
 }
 
+// Rows buffered per wavefront in a batch.  The workgroup's LDS (with a
+// histogram per wavefront) decides how many share a CU: it is handed out in
+// units of 1280 bytes, so five fit up to 32,000.  At 64 rows and 128 bins
+// it was 128 bytes over, a fifth of the persistent workgroups began only when
+// others had ended; 40 rows (which bind only below eight hits a row) fit up to
+// 256 bins: 556 -> 536 us for 96 frames, 62 M pairs.
+constexpr int kBatchRows = 40;
+
 // NeighborList and per-frame RDF (histograms [nframes][bins]) of a batch;
 // WPB wavefronts per workgroup.
 template <int DIM, int EXCL, int WPB>
@@ -31,7 +39,7 @@ __global__ void __launch_bounds__(WPB * kWave, 5) fill_batch_kernel(
 {
     extern __shared__ unsigned s_dyn[];  // one histogram per wavefront when bins are few
     __shared__ float4 s_off[WPB][27];
-    __shared__ FillLds<true> s_w[WPB];
+    __shared__ FillLds<true, kBatchRows> s_w[WPB];
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = uniform(threadIdx.x / kWave);
     StencilLds& S = s_w[wv].st;
@@ -42,10 +50,11 @@ __global__ void __launch_bounds__(WPB * kWave, 5) fill_batch_kernel(
         for (int b = lane; b < O.bins; b += kWave) h[b] = 0u;
     if (lane < kHitCap / 64) s_w[wv].starts[lane] = 0ull;
     wave_sync();
-    Filler<DIM, EXCL, true, true> F(s_w[wv], O, h, lane);
+    Filler<DIM, EXCL, true, true, kBatchRows> F(s_w[wv], O, h, lane);
     RunQueue R;
     unsigned long long* queue = B.queue + 8 * kQueueStride;
-    R.start(B, queue, WPB, lane);
+    R.start(B, WPB, wv);
+    const FrameSearch frames(B, lane);
     int f = -1, cur = 0, next = -1;
     GeomView V;
     int t, te;
@@ -57,12 +66,12 @@ __global__ void __launch_bounds__(WPB * kWave, 5) fill_batch_kernel(
                 // buffered hits belong to the old frame: write them and its bins first
                 if (F.nh > 0) F.flush();
                 if (lds_hist && f >= 0) merge_wave_hist(h, F.ghist, O.bins, lane);
-                f = frame_of(B, P.tile, lane);
+                f = frames.find(B, P.tile, lane);
+                cur = B.cell_base[f];
+                next = B.cell_base[f + 1];
                 V = load_frame(B, f, off, lane);
                 F.ghist = O.hist + (size_t)f * O.bins;
                 F.id_base = uniform(B.frames[f].point_base);
-                cur = B.cell_base[f];
-                next = B.cell_base[f + 1];
             }
             const int C = stencil<DIM>(in, V, P.tile, lane, S);
             const int ns = (C + kWave - 1) / kWave;

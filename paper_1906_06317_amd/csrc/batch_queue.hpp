@@ -30,12 +30,14 @@ namespace {
 // full cells takes a wavefront about 0.4 ms, so without the taper the last
 // runs leave most of the chip idle.  Draws are atomics on memory shared by
 // the XCDs, about 12 ns each on one line: each counter has its own 128-byte
-// line, the next run is drawn before the current one is worked, and a
-// wavefront whose queue is empty reads all counters at once instead of
-// drawing from each (that alone cost eight serialised draws per wavefront).
+// line, a wavefront's first run is the one of its own number, the next run is
+// drawn before the current one is worked, and a wavefront whose queue is empty
+// reads all counters at once instead of drawing from each (that alone cost
+// eight serialised draws per wavefront).
 // 96 frames, 1.2 M points, 62 M pairs: count 643 -> 214 us, fill 1233 -> 566
 // us (two first runs per wavefront instead of eight: 225 and 762 us; single
-// items throughout: 297 and 583 us).
+// items throughout: 297 and 583 us); with the first run not drawn and the first
+// frame probes kept, count 196 -> 186 us.
 struct RunQueue {
     int x;       // XCD whose queue is being drained
     int c0, n;   // that XCD's first item, and its items
@@ -59,24 +61,27 @@ struct RunQueue {
         t += k * len;
         return (int)(t < n ? t : n);
     }
+    // The first item of XCD x's queue.
+    static __device__ __forceinline__ int first(const BatchGeom& B, int x)
+    {
+        return (int)((long long)x * B.ncells * B.split / 8);
+    }
     __device__ __forceinline__ void set(const BatchGeom& B, int xcd)
     {
-        const long long items = (long long)B.ncells * B.split;
         x = xcd;
-        c0 = (int)(x * items / 8);
-        n = (int)((x + 1) * items / 8) - c0;
+        c0 = first(B, x);
+        n = first(B, x + 1) - c0;
     }
     __device__ __forceinline__ void draw(unsigned long long* queue, int lane)
     {
-        if (lane == 0) pend = atomicAdd(&queue[x * kQueueStride], 1ull);
+        if (lane == 0) pend = waves + atomicAdd(&queue[x * kQueueStride], 1ull);
     }
-    __device__ __forceinline__ void start(const BatchGeom& B, unsigned long long* queue, int wpb,
-                                          int lane)
+    // A wavefront's first run is the one of its own number within the XCD.
+    __device__ __forceinline__ void start(const BatchGeom& B, int wpb, int wv)
     {
         waves = (int)(gridDim.x >> 3) * wpb;
-        pend = 0;
+        pend = (unsigned long long)((blockIdx.x >> 3) * wpb + wv);
         set(B, blockIdx.x & 7);
-        draw(queue, lane);
     }
     // The next run [t, te) for this wavefront; false when every queue is empty.
     __device__ __forceinline__ bool next(const BatchGeom& B, unsigned long long* queue, int lane,
@@ -96,11 +101,10 @@ struct RunQueue {
             bool open = false;
             if (lane < 8) {
                 const int y = (x + 1 + lane) & 7;
-                const long long items = (long long)B.ncells * B.split;
-                const int m = (int)((y + 1) * items / 8) - (int)(y * items / 8);
+                const int m = first(B, y + 1) - first(B, y);
                 const unsigned long long d = __hip_atomic_load(
                     &queue[y * kQueueStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                open = run_at(B.run, waves, m, (long long)d, len) < m;
+                open = run_at(B.run, waves, m, waves + (long long)d, len) < m;
             }
             const unsigned long long some = __ballot(open);
             if (!some) return false;
@@ -110,22 +114,33 @@ struct RunQueue {
     }
 };
 
-// Frame of global cell `tile`: the last f with cell_base[f] <= tile, by a
-// 64-way search (the lanes probe 64 evenly spaced frames at once; a binary
-// search would chain a dependent read of memory per halving).
-__device__ __forceinline__ int frame_of(const BatchGeom& B, int tile, int lane)
-{
-    int lo = 0, n = B.nframes;  // the frame lies in [lo, lo + n)
-    while (n > 1) {
-        const int step = (n + kWave - 1) / kWave;
-        const int f = lo + lane * step;
-        const bool at = lane * step < n && B.cell_base[f] <= tile;
-        const int hit = __popcll(__ballot(at)) - 1;  // lane 0 always probes a frame at or below
-        lo += hit * step;
-        n = min(step, n - hit * step);
+// Frame of a global cell: the last f with cell_base[f] <= tile, by a 64-way
+// search (the lanes probe 64 evenly spaced frames at once; a binary search
+// would chain a dependent read of memory per halving).  The first probes are
+// the same for every cell and stay in a register.
+struct FrameSearch {
+    int step, base;
+
+    __device__ __forceinline__ FrameSearch(const BatchGeom& B, int lane)
+    {
+        step = (B.nframes + kWave - 1) / kWave;
+        base = lane * step < B.nframes ? B.cell_base[lane * step] : INT_MAX;
     }
-    return uniform(lo);
-}
+    __device__ __forceinline__ int find(const BatchGeom& B, int tile, int lane) const
+    {
+        // lane 0 always probes a frame at or below
+        int lo = (__popcll(__ballot(base <= tile)) - 1) * step;
+        int n = min(step, B.nframes - lo);  // the frame lies in [lo, lo + n)
+        while (n > 1) {
+            const int st = (n + kWave - 1) / kWave;
+            const bool at = lane * st < n && B.cell_base[lo + lane * st] <= tile;
+            const int hit = __popcll(__ballot(at)) - 1;
+            lo += hit * st;
+            n = min(st, n - hit * st);
+        }
+        return uniform(lo);
+    }
+};
 
 // Loads frame f's geometry: the view in scalar registers, the stencil
 // offsets into this wavefront's LDS.
@@ -151,10 +166,7 @@ template <typename K>
 inline int batch_blocks(K kernel, int threads, size_t lds, int blocks_cap)
 {
     const int cus = device_cus();
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
+    int per_cu = resident_per_cu(kernel, threads, lds);
     if (blocks_cap > 0 && per_cu > blocks_cap) per_cu = blocks_cap;
     return (cus * per_cu + 7) / 8 * 8;
 }

@@ -9,7 +9,7 @@
 // cover about 10.5 of the 27 cells' volume, of which a query's ball is 4.2.
 // The stencil is streamed cell by cell, tested against the box (cutoff and
 // the rounding of the tests, r2prune), and what is left is compacted into an
-// LDS stage, from which all the queries take it four register slots at a
+// LDS stage, from which all the queries take it three register slots at a
 // time; the hits' r^2 are compacted again and binned 64 at a time.  In or out
 // is decided by the expanded test where the host allows it and by r^2 itself
 // elsewhere, and bins come from the difference of coordinates, as in the fill

@@ -594,16 +594,33 @@ __global__ void __launch_bounds__(256) partial_sum_stage1(const T* __restrict__ 
         level2[(size_t)blockIdx.y * W + w] = (s[0][lane] + s[1][lane]) + (s[2][lane] + s[3][lane]);
 }
 
+// Workgroups of `kernel` (`threads` threads, `lds` bytes of dynamic LDS) that
+// are resident on a CU at once.  The runtime's figure divides the LDS by the
+// bytes asked for; it is handed out in units of 1280 bytes, which can be one
+// workgroup fewer, and a persistent workgroup beyond the resident ones starts
+// its share of the work only when another has ended.
+template <typename K>
+inline int resident_per_cu(K kernel, int threads, size_t lds)
+{
+    constexpr size_t kUnit = 1280, kLds = 163840;
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess ||
+        per_cu < 1)
+        return 1;
+    hipFuncAttributes fa;
+    if (hipFuncGetAttributes(&fa, (const void*)kernel) != hipSuccess) return per_cu;
+    const size_t units = (fa.sharedSizeBytes + lds + kUnit - 1) / kUnit;
+    const int fit = units ? (int)(kLds / (units * kUnit)) : per_cu;
+    return per_cu < fit ? per_cu : (fit < 1 ? 1 : fit);
+}
+
 // Workgroups for a persistent launch of `kernel`: as many as fit on the
 // device at once, at least one home cell per wavefront, a multiple of 8.
 template <typename K>
 inline int resident_blocks(K kernel, size_t lds, long long ncells)
 {
     const int cus = device_cus();
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, lds) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
+    const int per_cu = resident_per_cu(kernel, kBlock, lds);
     long long want = (ncells + kWavesPerBlock - 1) / kWavesPerBlock;
     const long long cap = (long long)cus * per_cu;
     if (want > cap) want = cap;

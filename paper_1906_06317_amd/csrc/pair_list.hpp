@@ -46,7 +46,7 @@ namespace {
 using namespace pair;
 
 constexpr int kHitCap = 320;  // hits buffered per wavefront between flushes
-constexpr int kRows = 64;     // rows buffered per wavefront
+constexpr int kRows = 64;     // rows buffered per wavefront (in a batch, kBatchRows)
 constexpr int kFillSlots = 10;  // register slots of the fill pass (it needs more registers)
 static_assert(kFillSlots * kWave <= kCandCap, "a whole stencil fits the r^2 buffer");
 constexpr int kMaxBatchLdsBins = 1024;  // per-wavefront histograms of a batch up to this size
@@ -223,28 +223,28 @@ struct FillOut {
 // candidate's coordinates (its exact distance is recomputed at the flush)
 // and rows are whole; for the histogram alone, a hit keeps only its exact
 // r^2 from the difference form.
-template <bool NL>
+template <bool NL, int ROWS = kRows>
 struct FillLds;
 
-template <>
-struct FillLds<true> {
+template <int ROWS>
+struct FillLds<true, ROWS> {
     float4 hit[kHitCap];               // candidate xyz relative to the home centre, index bits
-    float4 rq[kRows];                  // each non-empty row's query xyz, index bits
-    long long base[kRows];             // offsets[q] - first buffered hit of the row
+    float4 rq[ROWS];                   // each non-empty row's query xyz, index bits
+    long long base[ROWS];              // offsets[q] - first buffered hit of the row
     unsigned long long starts[kHitCap / 64];  // bit e: a non-empty row starts at hit e
     StencilLds st;
 };
 
-template <>
-struct FillLds<false> {
+template <int ROWS>
+struct FillLds<false, ROWS> {
     float r2[kCandCap];
     StencilLds st;
 };
 
 // Per-wavefront state of the fill pass.
-template <int DIM, int EXCL, bool NL, bool HIST>
+template <int DIM, int EXCL, bool NL, bool HIST, int ROWS = kRows>
 struct Filler {
-    FillLds<NL>& W;
+    FillLds<NL, ROWS>& W;
     const FillOut O;
     unsigned* hist_lds;  // NULL: bin straight into ghist
     unsigned long long* ghist;  // the histogram in global memory (the frame's, in a batch)
@@ -255,7 +255,7 @@ struct Filler {
     int selfs;  // own entries binned by the histogram-only path (all at r = 0)
     bool over;
 
-    __device__ Filler(FillLds<NL>& w, const FillOut& o, unsigned* h, int l)
+    __device__ Filler(FillLds<NL, ROWS>& w, const FillOut& o, unsigned* h, int l)
         : W(w), O(o), hist_lds(h), ghist(o.hist), id_base(0), lane(l), nh(0), nrows(0), selfs(0),
           over(false)
     {
@@ -434,10 +434,10 @@ struct Filler {
 };
 
 // Queries [q0, q1) of the home cell whose first query is qc.
-template <int DIM, int EXCL, bool NL, bool HIST, int NS>
+template <int DIM, int EXCL, bool NL, bool HIST, int NS, int ROWS>
 __device__ __forceinline__ void fill_tile(const PairIn& in, const GeomView& G, const StencilLds& S,
                                           const float4* off, int C, int qc, int q0, int q1,
-                                          Filler<DIM, EXCL, NL, HIST>& F)
+                                          Filler<DIM, EXCL, NL, HIST, ROWS>& F)
 {
     const int lane = F.lane;
     Slots<DIM, NS> c;
@@ -469,7 +469,7 @@ __device__ __forceinline__ void fill_tile(const PairIn& in, const GeomView& G, c
                 // two rows at once when both fit the buffer
                 const int need_b = t + 1 < Q.n ? lane_of(rl_v, t + 1) : kHitCap + 1;
                 if (need + need_b <= kHitCap) {
-                    if (F.nh + need + need_b > kHitCap || F.nrows + 2 > kRows) F.flush();
+                    if (F.nh + need + need_b > kHitCap || F.nrows + 2 > ROWS) F.flush();
                     const int rsa = F.nh;
                     const int rsb = rsa + need;
                     const int self_b = (c0 - qc) + t + 1 < kWave ? (c0 - qc) + t + 1 : -1;
@@ -497,7 +497,7 @@ __device__ __forceinline__ void fill_tile(const PairIn& in, const GeomView& G, c
                     ++t;
                     continue;
                 }
-                if (F.nh + need > kHitCap || F.nrows == kRows) F.flush();
+                if (F.nh + need > kHitCap || F.nrows == ROWS) F.flush();
             } else {
                 // the histogram alone: at most every candidate
                 if (F.nh + C > kCandCap) F.flush();
@@ -521,10 +521,10 @@ __device__ __forceinline__ void fill_tile(const PairIn& in, const GeomView& G, c
     }
 }
 
-template <int DIM, int EXCL, bool NL, bool HIST>
+template <int DIM, int EXCL, bool NL, bool HIST, int ROWS>
 __device__ __forceinline__ void fill_chunked(const PairIn& in, const GeomView& G,
                                              const StencilLds& S, const float4* off, int C,
-                                             int q0, int q1, Filler<DIM, EXCL, NL, HIST>& F)
+                                             int q0, int q1, Filler<DIM, EXCL, NL, HIST, ROWS>& F)
 {
     const int lane = F.lane;
     const float r2max = G.r2max;

@@ -430,13 +430,8 @@ __global__ void __launch_bounds__(256) smooth_reduce_kernel(const double* __rest
 template <int DIM, bool BWD, bool FAST>
 int occupancy_blocks(size_t dyn)
 {
-    const int cus = device_cus();
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, smooth_kernel<DIM, BWD, FAST>,
-                                                     kBlock, dyn) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
-    return (cus * per_cu + 7) / 8 * 8;
+    const int per_cu = resident_per_cu(smooth_kernel<DIM, BWD, FAST>, kBlock, dyn);
+    return (device_cus() * per_cu + 7) / 8 * 8;
 }
 
 bool fixed_bins(int bins) { return bins <= kSmFixedBins; }
