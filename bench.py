@@ -772,10 +772,10 @@ def row_smooth(ppa, hip):
                                      "achieved": ADJOINT_TERM_OPS * terms / (bwd_ms * 1e-3),
                                      "frac": ADJOINT_TERM_OPS * terms / (bwd_ms * 1e-3)
                                      / VALU_LANE_OPS,
-                                     "note": "adjoint: Gaussians by recurrence, 7 lane "
-                                             "operations per window term (4 float32 "
-                                             "multiplies, an add, a conversion and a "
-                                             "float64 add)"}}}
+                                     "note": "the work of walking every window (Gaussians "
+                                             "by recurrence, 7 lane operations per term); "
+                                             "the adjoint reads A(r) from a table of cubics "
+                                             "instead, so this is an equivalent rate"}}}
 
 
 def _cpu_model():
