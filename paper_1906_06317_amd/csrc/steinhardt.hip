@@ -86,18 +86,33 @@ constexpr double step_ratio(int l, int m)
     return ((double)(l - 1) * (l - 1) - (double)m * m) / (4.0 * (l - 1) * (l - 1) - 1.0);
 }
 // The factors left out of q_lm's terms: the sectoral constant c_m (with the
-// Condon-Shortley phase) times the product of a_l for l = m + 1 .. L.
+// Condon-Shortley phase) times the product of a_l for l = m + 1 .. L.  Their
+// square is a ratio of whole numbers, kept in lowest terms up to the division.
 template <int L>
 struct SectorScale {
     double v[L + 1];
 
+    static constexpr unsigned long long gcd(unsigned long long a, unsigned long long b)
+    {
+        while (b) {
+            const unsigned long long t = a % b;
+            a = b;
+            b = t;
+        }
+        return a;
+    }
     constexpr SectorScale() : v()
     {
         for (int m = 0; m <= L; ++m) {
-            double sq = 1.0;
-            for (int k = 1; k <= m; ++k) sq *= (2.0 * k + 1.0) / (2.0 * k);
-            for (int l = m + 1; l <= L; ++l)
-                sq *= (4.0 * l * l - 1.0) / ((double)l * l - (double)m * m);
+            unsigned long long num = 1, den = 1;
+            for (int k = 1; k <= L; ++k) {
+                num *= k <= m ? 2 * k + 1 : 4 * k * k - 1;
+                den *= k <= m ? 2 * k : k * k - m * m;
+                const unsigned long long g = gcd(num, den);
+                num /= g;
+                den /= g;
+            }
+            const double sq = (double)num / (double)den;
             double y = sq;  // its square root, by Newton's iteration
             for (int k = 0; k < 64; ++k) y = 0.5 * (y + sq / y);
             v[m] = (m & 1 ? -1.0 : 1.0) * kInvSqrt4Pi * y;
@@ -162,7 +177,12 @@ __global__ void __launch_bounds__(kStBlock, (L <= 6 ? 5 : 1)) steinhardt_kernel(
         }
         if (r2 == 0.0) continue;
         ++nb;
-        const double inv_r = inv_sqrt(r2);
+        // its rounding error enters q_lm l-fold: the product's low part keeps it to
+        // the last bit
+        const double y = __builtin_amdgcn_rsq(r2);
+        const double h = r2 * y;
+        const double c = fma(-y, fma(r2, y, -h), fma(-h, y, 1.0));
+        const double inv_r = fma(y, c * fma(c, 0.375, 0.5), y);
         const double x = d[2] * inv_r;                     // cos(theta)
         const double ur = d[0] * inv_r, ui = d[1] * inv_r; // sin(theta) e^{i phi}
         // (sin(theta) e^{i phi})^m times P_L^m / P_m^m by the upward recurrence in

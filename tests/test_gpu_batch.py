@@ -313,3 +313,22 @@ def test_queue_runs_parts_and_frame_search(ppa, count, n_lo, n_hi):
         assert torch.equal(nl.dist[first:last], one.dist), f
         first = last
     assert first == nl.n_pairs
+
+
+@pytest.mark.parametrize("r_max,bins", [(0.5, 1), (0.9, 256), (1.25, 300), (1.4, 1025)])
+def test_short_rows_fill_the_row_buffer(ppa, r_max, bins):
+    """Rows of none to about ten entries, so the buffered rows run out before
+    the buffered hits do, at histograms inside and past the wavefronts' LDS,
+    against the oracle (a batch's cells are not widened where points are few, so
+    a row's order is not that of a call per frame)."""
+    frames = _frames(900 + bins, 5, 2000, 9000)
+    boxes = [ppa.Box(s.L, s.tilt, s.dim) for s in frames]
+    plan = ppa.BatchPlan(boxes, [s.points.shape[0] for s in frames], bins, r_max)
+    hist, nl = plan.run(np.concatenate([s.points for s in frames]))
+    pb = plan.offsets_host
+    for f, s in enumerate(frames):
+        ob = oracle.make_box(s.L, s.tilt, s.dim)
+        lo, hi, _ = oracle.rdf_counts(ob, s.points, bins, r_max)
+        check_hist(hist[f].cpu().numpy(), lo, hi)
+        ref = oracle.ball_query(ob, s.points, r_max)
+        check_rows(_FrameNL(nl, pb[f], pb[f + 1]), ref, range(s.points.shape[0]), r_max)
