@@ -17,7 +17,7 @@ __global__ void __launch_bounds__(WPB * kWave, 5) count_batch_kernel(
     const int wv = uniform(threadIdx.x / kWave);
     StencilLds& S = s_st[wv];
     float4* off = s_off[wv];
-    RunQueue R;
+    RunQueue<8> R;
     R.start(B, WPB, wv);
     const FrameSearch frames(B, lane);
     int f = -1, cur = 0, next = -1;

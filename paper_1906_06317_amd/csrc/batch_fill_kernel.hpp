@@ -51,7 +51,7 @@ __global__ void __launch_bounds__(WPB * kWave, 5) fill_batch_kernel(
     if (lane < kHitCap / 64) s_w[wv].starts[lane] = 0ull;
     wave_sync();
     Filler<DIM, EXCL, true, true, kBatchRows> F(s_w[wv], O, h, lane);
-    RunQueue R;
+    RunQueue<32> R;
     unsigned long long* queue = B.queue + 8 * kQueueStride;
     R.start(B, WPB, wv);
     const FrameSearch frames(B, lane);

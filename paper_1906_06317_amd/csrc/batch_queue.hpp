@@ -24,7 +24,7 @@ namespace {
 // dear cells) finish together.  Every wavefront ends when all eight queues
 // are empty.
 //
-// Runs are B.run items long (fewer when there are not eight such runs per
+// Runs are B.run items long (fewer when there are not PER such runs per
 // wavefront) until two runs per wavefront of the XCD are left, then halve
 // once per wavefront, down to single items: a run of 16
 // full cells takes a wavefront about 0.4 ms, so without the taper the last
@@ -35,9 +35,13 @@ namespace {
 // reads all counters at once instead of drawing from each (that alone cost
 // eight serialised draws per wavefront).
 // 96 frames, 1.2 M points, 62 M pairs: count 643 -> 214 us, fill 1233 -> 566
-// us (two first runs per wavefront instead of eight: 225 and 762 us; single
-// items throughout: 297 and 583 us); with the first run not drawn and the first
-// frame probes kept, count 196 -> 186 us.
+// us (two first runs per wavefront instead of eight: 225 and 762 us); with the
+// first run not drawn and the first frame probes kept, count 196 -> 186 us.
+// PER is 8 in the count pass, whose cells are short against a draw (at 16 the
+// frames above go cell by cell: 265 us), and 32 in the fill pass, whose last
+// runs cost more than its draws: a batch of 256 frames, 11 M points, at most 16
+// cells a run, 6.08 -> 5.76 ms with 32 instead of 8.
+template <int PER>
 struct RunQueue {
     int x;       // XCD whose queue is being drained
     int c0, n;   // that XCD's first item, and its items
@@ -47,7 +51,7 @@ struct RunQueue {
     // Items of the k-th run of a queue of n items: [t, t + len); t >= n past the end.
     static __device__ __forceinline__ int run_at(int run, int waves, int n, long long k, int& len)
     {
-        run = max(1, min(run, n / (8 * waves)));
+        run = max(1, min(run, n / (PER * waves)));
         const long long whole = max(0LL, ((long long)n - 2LL * waves * run) / run);
         len = run;
         if (k < whole) return (int)(k * run);
