@@ -55,8 +55,8 @@ struct SmoothLds {
 // one term to a bin, so after kSmFold pairs the limbs, below 2^20 each, are
 // folded into the float64 histogram before a sum can pass 2^32.
 // 131,072 points, 21 bins a window: 374 us with float64 atomics, 340 now,
-// bound by vector issue (950 instructions a particle, half of them the
-// window terms).
+// bound by vector issue (950 instructions a particle, half of them the window
+// terms; 66 % busy) and the LDS adds (67 % of what LDS adds alone reach).
 constexpr int kSmFold = 4000;
 constexpr int kSmFixedBins = 1024;  // limbs of more bins would cost resident workgroups
 static_assert(kSmFold <= 4095, "sums of 20-bit limbs must stay below 2^32");
