@@ -1010,12 +1010,6 @@ int run_smooth(const ppa_box* box, const float* pts, int64_t n, int32_t bins, fl
     const double drf = (double)(float)A.dr;  // the step the kernel adds
     A.step2 = (float)exp2(-2.0 * (double)A.k2 * drf * drf);
     A.hscale = (float)(A.dr / (sg * sqrt(2.0 * M_PI)));
-    // 2^e is at least hscale, the largest term; strictly above it, so that the
-    // high limb of a term stays below 2^20
-    int e = 0;
-    (void)frexpf(A.hscale, &e);
-    A.hfix = ldexpf(A.hscale, 20 - e);
-    A.hunit = ldexp(1.0, e - 40);
     A.gscale = (float)(A.dr / (sg * sg * sg * sqrt(2.0 * M_PI)));
     A.table = table;
     A.nodes = P.nodes;

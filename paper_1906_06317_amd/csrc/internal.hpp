@@ -441,8 +441,6 @@ struct SmoothArgs {
     float k2;                 // log2(e) / (2 sigma^2)
     float step2;              // 2^(-2 k2 dr^2): ratio of consecutive bins' Gaussian factors
     float hscale;             // dr / (sigma sqrt(2 pi)): forward weight of exp(-u^2/2s^2)
-    float hfix;               // hscale 2^(20-e) with hscale <= 2^e: terms in fixed point
-    double hunit;             // 2^(e-40): the value of the low limb's unit
     float gscale;             // dr / (sigma^3 sqrt(2 pi)): adjoint weight of u exp(-u^2/2s^2)
     int split;                // work units per home cell (its queries in parts)
     double* partial;          // forward: [gridDim.x][bins]

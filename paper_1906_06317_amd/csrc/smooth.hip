@@ -18,9 +18,8 @@
 // float64 from the stored cell-local coordinates and a float64 stencil
 // offset, so the distance entering the Gaussian is exact to the rounding of
 // the stored coordinates; the window terms are then evaluated in float32
-// with the hardware exp2.  The forward adds each term into a per-wavefront LDS
-// histogram in fixed point and folds that into a float64 one per workgroup
-// (partials summed by a second kernel); the adjoint
+// with the hardware exp2.  The forward adds each term into a float64 LDS
+// histogram per workgroup (partials summed by a second kernel); the adjoint
 // gathers each query's row in float64, so every particle's gradient is
 // written once, by the wavefront that owns it, with no atomics.  For given
 // G, A(r) is one smooth function of r for every pair: a small kernel tabulates
@@ -47,20 +46,12 @@ struct SmoothLds {
     StencilLds st;
 };
 
-// Fixed-point forward histogram.  float64 LDS atomics run at about 1.4 lanes
-// a clock per CU whatever the addresses (44 cycles for a wavefront's), 32-bit
-// integer ones at about 8: a term, a float32 below 2^e, is held as two 20-bit
-// limbs, floor(v 2^(20-e)) and the next 20 bits, added by two integer atomics
-// (2^(e-40) resolution, 4.5e-13 of the largest term).  A pair adds at most
-// one term to a bin, so after kSmFold pairs the limbs, below 2^20 each, are
-// folded into the float64 histogram before a sum can pass 2^32.
-// 131,072 points, 21 bins a window: 374 us with float64 atomics, 340 now,
-// bound by vector issue (950 instructions a particle, half of them the window
-// terms; 66 % busy) and the LDS adds (67 % of what LDS adds alone reach).
-constexpr int kSmFold = 4000;
-constexpr int kSmFixedBins = 1024;  // limbs of more bins would cost resident workgroups
-static_assert(kSmFold <= 4095, "sums of 20-bit limbs must stay below 2^32");
-
+// The forward is bound by its float64 LDS atomics (about 1.4 lanes a clock per CU
+// whatever the addresses) and by vector issue: 131,072 points, 21 bins a
+// window, 374 us.  Two 20-bit limbs of a fixed-point sum by 32-bit atomics took 340 us,
+// but keep a term's 24 bits only down to 2^-17 of the largest one: 5.6e-5 off at
+// 5 sigma and nothing left past 7.4.  With float64 sums for the smaller terms, or with
+// three pairs of limbs 17 bits apart, both exact, the whole call took 440 us instead of 415.
 template <int BUF>
 struct SmoothShared {
     float4 off[27];
@@ -144,12 +135,10 @@ __device__ __forceinline__ int buffer_query(const SmSlots<DIM, NS>& c, SmoothLds
     return nh;
 }
 
-// Forward flush: every buffered pair's window terms, into the wavefront's
-// fixed-point limbs (FIXED) or the float64 LDS histogram.
-template <int DIM, bool FIXED, int BUF>
+// Forward flush: every buffered pair's window terms into the LDS histogram.
+template <int DIM, int BUF>
 __device__ __forceinline__ void flush_fwd(const SmoothArgs& a, const SmoothShared<BUF>& L,
-                                          SmoothLds<BUF>& W, double* hist, unsigned* limbs, int nh,
-                                          int lane)
+                                          SmoothLds<BUF>& W, double* hist, int nh, int lane)
 {
     wave_sync();
     const float drf = (float)a.dr;
@@ -160,47 +149,16 @@ __device__ __forceinline__ void flush_fwd(const SmoothArgs& a, const SmoothShare
         int b0, b1;
         float u0;
         window(a, r, b0, b1, u0);
+        // each lane starts its walk at a different bin of its window, so the
+        // lanes of one instruction rarely add to the same bin
         const int nb = b1 - b0 + 1;
-        if constexpr (FIXED) {
-            unsigned* hi = limbs + b0;
-            unsigned* lo = hi + a.bins;
-            float m = 0.f;
+        int m = nb > 0 ? lane % nb : 0;
 #pragma unroll 4
-            for (int j = 0; j < nb; ++j) {
-                const float u = fmaf(m, drf, u0);
-                // hfix is hscale times a power of two: the same rounding
-                const float v = a.hfix * __builtin_amdgcn_exp2f(-(u * u) * a.k2);
-                atomicAdd(&hi[j], (unsigned)v);
-                atomicAdd(&lo[j], (unsigned)(__builtin_amdgcn_fractf(v) * 1048576.f));
-                m += 1.f;
-            }
-        } else {
-            // each lane starts its walk at a different bin of its window, so the
-            // lanes of one instruction rarely add to the same bin
-            int m = nb > 0 ? lane % nb : 0;
-#pragma unroll 4
-            for (int j = 0; j < nb; ++j) {
-                const float u = fmaf((float)m, drf, u0);
-                const float v = a.hscale * __builtin_amdgcn_exp2f(-(u * u) * a.k2);
-                atomicAdd(&hist[b0 + m], (double)v);
-                m = m + 1 == nb ? 0 : m + 1;
-            }
-        }
-    }
-    wave_sync();
-}
-
-// Folds the wavefront's limbs into the float64 histogram and clears them.
-__device__ __forceinline__ void fold_limbs(const SmoothArgs& a, double* hist, unsigned* limbs,
-                                           int lane)
-{
-    wave_sync();
-    for (int b = lane; b < a.bins; b += kWave) {
-        const unsigned hi = limbs[b], lo = limbs[a.bins + b];
-        if (hi | lo) {
-            atomicAdd(&hist[b], fma((double)hi, 1048576.0, (double)lo) * a.hunit);
-            limbs[b] = 0u;
-            limbs[a.bins + b] = 0u;
+        for (int j = 0; j < nb; ++j) {
+            const float u = fmaf((float)m, drf, u0);
+            const float v = a.hscale * __builtin_amdgcn_exp2f(-(u * u) * a.k2);
+            atomicAdd(&hist[b0 + m], (double)v);
+            m = m + 1 == nb ? 0 : m + 1;
         }
     }
     wave_sync();
@@ -308,15 +266,13 @@ __device__ __forceinline__ void flush_bwd(const SmoothArgs& a, const SmoothShare
     wave_sync();
 }
 
-// FAST: fixed-point limbs (forward), tabulated A (adjoint).
-template <int DIM, bool BWD, bool FAST>
+// TABLE: the adjoint with tabulated A.
+template <int DIM, bool BWD, bool TABLE>
 __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
 {
-    constexpr bool FIXED = !BWD && FAST, TABLE = BWD && FAST;
     // the adjoint flushes after every chunk of a query
     constexpr int BUF = BWD ? kSmSlots * kWave : kSmBuf;
-    // forward: histogram (float64), then with FIXED two limbs per bin and
-    // wavefront; adjoint without the table: G (float32)
+    // forward: histogram (float64); adjoint without the table: G (float32)
     extern __shared__ double s_dyn[];
     __shared__ SmoothShared<BUF> L;
     const int lane = threadIdx.x & (kWave - 1);
@@ -336,12 +292,6 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
         else
             hist[b] = 0.0;
     }
-    unsigned* limbs = nullptr;
-    if (FIXED) {
-        unsigned* all = reinterpret_cast<unsigned*>(hist + a.bins);
-        for (int b = threadIdx.x; b < 2 * kWavesPerBlock * a.bins; b += kBlock) all[b] = 0u;
-        limbs = all + (size_t)wv * 2 * a.bins;
-    }
     __syncthreads();
     const PairIn in{a.cand, a.cand_start, a.cand, a.cand_start};
     const float r2s = G.r2max;
@@ -350,14 +300,8 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
     int t0, t1, stride;
     wave_tiles_interleaved<kWavesPerBlock>(G.ncells * a.split, wv, t0, t1, stride);
     int nh = 0;
-    int added = 0;  // pairs in the limbs
     auto flush = [&]() {
-        if (FIXED && added + nh > kSmFold) {
-            fold_limbs(a, hist, limbs, lane);
-            added = 0;
-        }
-        flush_fwd<DIM, FIXED, BUF>(a, L, W, hist, limbs, nh, lane);
-        added += nh;
+        flush_fwd<DIM, BUF>(a, L, W, hist, nh, lane);
         nh = 0;
     };
     for (int unit = t0; unit < t1; unit += stride) {
@@ -407,7 +351,6 @@ __global__ void __launch_bounds__(kBlock) smooth_kernel(const SmoothArgs a)
         }
     }
     if (!BWD) {
-        if (FIXED) fold_limbs(a, hist, limbs, lane);
         __syncthreads();
         double* out = a.partial + (size_t)blockIdx.x * a.bins;
         for (int b = threadIdx.x; b < a.bins; b += kBlock) out[b] = hist[b];
@@ -427,30 +370,11 @@ __global__ void __launch_bounds__(256) smooth_reduce_kernel(const double* __rest
     h[b] += sum;
 }
 
-template <int DIM, bool BWD, bool FAST>
+template <int DIM, bool BWD, bool TABLE>
 int occupancy_blocks(size_t dyn)
 {
-    const int per_cu = resident_per_cu(smooth_kernel<DIM, BWD, FAST>, kBlock, dyn);
+    const int per_cu = resident_per_cu(smooth_kernel<DIM, BWD, TABLE>, kBlock, dyn);
     return (device_cus() * per_cu + 7) / 8 * 8;
-}
-
-bool fixed_bins(int bins) { return bins <= kSmFixedBins; }
-
-size_t fwd_lds(int bins)
-{
-    return (sizeof(double) + (fixed_bins(bins) ? 2 * kWavesPerBlock * sizeof(unsigned) : 0)) *
-           (size_t)bins;
-}
-
-template <int DIM>
-void launch_fwd_dim(const SmoothArgs& a, int blocks, hipStream_t s)
-{
-    const size_t dyn = fwd_lds(a.bins);
-    if (fixed_bins(a.bins))
-        hipLaunchKernelGGL((smooth_kernel<DIM, false, true>), dim3(blocks), dim3(kBlock), dyn, s, a);
-    else
-        hipLaunchKernelGGL((smooth_kernel<DIM, false, false>), dim3(blocks), dim3(kBlock), dyn, s,
-                           a);
 }
 
 }  // namespace
@@ -459,32 +383,28 @@ void launch_fwd_dim(const SmoothArgs& a, int blocks, hipStream_t s)
 // sized by it): every workgroup the device holds at once, a multiple of 8.
 int smooth_workgroups(bool adjoint, int dim, int bins, bool table)
 {
-    if (adjoint) {
-        const size_t dyn = sizeof(float) * (size_t)bins;
-        if (table)
-            return dim == 3 ? occupancy_blocks<3, true, true>(0) : occupancy_blocks<2, true, true>(0);
-        return dim == 3 ? occupancy_blocks<3, true, false>(dyn)
-                        : occupancy_blocks<2, true, false>(dyn);
+    if (!adjoint) {
+        const size_t dyn = sizeof(double) * (size_t)bins;
+        return dim == 3 ? occupancy_blocks<3, false, false>(dyn)
+                        : occupancy_blocks<2, false, false>(dyn);
     }
-    const size_t dyn = fwd_lds(bins);
-    if (fixed_bins(bins))
-        return dim == 3 ? occupancy_blocks<3, false, true>(dyn)
-                        : occupancy_blocks<2, false, true>(dyn);
-    return dim == 3 ? occupancy_blocks<3, false, false>(dyn)
-                    : occupancy_blocks<2, false, false>(dyn);
+    if (table) return dim == 3 ? occupancy_blocks<3, true, true>(0) : occupancy_blocks<2, true, true>(0);
+    const size_t dyn = sizeof(float) * (size_t)bins;
+    return dim == 3 ? occupancy_blocks<3, true, false>(dyn) : occupancy_blocks<2, true, false>(dyn);
 }
 
 void launch_smooth_fwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s)
 {
+    const size_t dyn = sizeof(double) * (size_t)a.bins;
     if (dim == 3)
-        launch_fwd_dim<3>(a, blocks, s);
+        hipLaunchKernelGGL((smooth_kernel<3, false, false>), dim3(blocks), dim3(kBlock), dyn, s, a);
     else
-        launch_fwd_dim<2>(a, blocks, s);
+        hipLaunchKernelGGL((smooth_kernel<2, false, false>), dim3(blocks), dim3(kBlock), dyn, s, a);
     const int rows = partial_rows(blocks);
     hipLaunchKernelGGL(partial_sum_stage1<double>, dim3((a.bins + 63) / 64, rows), dim3(256), 0, s,
                        a.partial, blocks, a.bins, kPartialRowsPer, a.level2);
-    hipLaunchKernelGGL(smooth_reduce_kernel, dim3((a.bins + 255) / 256), dim3(256), 0, s,
-                       a.level2, rows, a.bins, a.h);
+    hipLaunchKernelGGL(smooth_reduce_kernel, dim3((a.bins + 255) / 256), dim3(256), 0, s, a.level2,
+                       rows, a.bins, a.h);
 }
 
 void launch_smooth_bwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s)

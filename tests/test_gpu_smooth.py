@@ -249,3 +249,33 @@ def test_adjoint_table_and_its_limit(ppa, bins, r_max, sigma):
     d = g.astype(np.float64) - g_ref
     assert np.linalg.norm(d) < tol * np.linalg.norm(g_ref)
     assert np.abs(d).max() < tol * np.abs(g_ref).max()
+
+
+def _lone_pairs(r):
+    """27 pairs with no other neighbours, pair k at distance r[k] along x, on
+    positions that the cell-local coordinates hold exactly (64 cells of width 11)."""
+    import paper_1906_06317_amd as m
+    a = np.stack(np.meshgrid([-14.25, 0.25, 14.75], [-14.25, 0.25, 14.75], [-14.25, 0.25, 14.75],
+                             indexing="ij"), -1).reshape(-1, 3)
+    b = a.copy()
+    b[:, 0] += r
+    return m.Box((44.0, 44.0, 44.0), (0.0, 0.0, 0.0), 3), np.concatenate([a, b]).astype(np.float32)
+
+
+@pytest.mark.parametrize("bins", [64, 256, 1024, 1280])
+def test_forward_tails(ppa, bins):
+    """Bins that only the tails of a pair's Gaussian reach, out to 8 sigma, hold
+    their terms to float32 accuracy relative to themselves."""
+    r_max, sg, r = 4.0, 0.125, 2.1318359375
+    dr = r_max / bins
+    box, pts = _lone_pairs(np.full(27, r))
+    h = ppa.smooth_rdf_h(box, pts, bins, r_max, sg).cpu().numpy()
+    u = (np.arange(bins) + 0.5) * dr - r
+    t = np.abs(u) / sg
+    ref = 54 * dr / (sg * math.sqrt(2 * math.pi)) * np.exp(-0.5 * t * t)
+    inside = t < 8.0 - 1e-5
+    # u off by up to 32 sigma 2^-24 (three roundings of up to 16 sigma), its
+    # square times a constant by 3 roundings, the exponential by 2 ulp
+    tol = 2.0 ** -24 * (6.0 + 32.0 * t + 1.5 * t * t)
+    assert inside.sum() > 8 and np.all(np.abs(h - ref)[inside] <= (tol * ref)[inside])
+    assert np.all(h[t > 8.0 + 1e-5] == 0.0)
