@@ -919,8 +919,27 @@ struct SmoothPlan {
     Grid g;
     double r_s;  // pair cutoff r_max + 8 sigma
     int blocks;
-    int nodes;   // adjoint: table nodes, sigma / 16 apart (0: too many, no table)
+    bool adjoint;
+    int nodes;   // adjoint: table nodes, sigma / kSmoothNodes apart (0: no table)
 };
+
+// Nodes of the adjoint's table, or 0 where the window terms cost less than the
+// table: a node costs its lanes and terms, about five of the units in which a pair's window
+// costs its terms (below 8192 particles or 32 neighbours the chip is not full and a
+// call takes as long).  Table and window terms, whole call: 1000 particles, 12 terms, 10,112 nodes 63
+// and 69 us; 8000, 1.5 terms, 192,512 nodes 81 and 74; 8000, 23 terms, 96,512 nodes
+// 84 and 95; 131,072, 12 terms, 10,112 nodes 241 and 315.
+int smooth_nodes(const BoxPrep& bp, int64_t n, int32_t bins, double r_max, double sigma, double r_s)
+{
+    const double nodes = ceil(r_s * kSmoothNodes / sigma) + 2.0;
+    if (nodes > kSmoothMaxNodes) return 0;
+    const double terms = smooth_terms(bins, r_max, sigma);
+    const double area = bp.M[0][0] * bp.M[1][1];
+    const double rho = (double)n / (bp.dim == 3 ? area * bp.M[2][2] : area);
+    const double near = rho * M_PI * r_s * r_s * (bp.dim == 3 ? 4.0 / 3.0 * r_s : 1.0);
+    const double pairs = fmax(n * near, 8192.0 * fmax(near, 32.0));
+    return 5.0 * nodes * (smooth_lanes(terms) + terms) <= pairs * terms ? (int)nodes : 0;
+}
 
 int smooth_plan(const BoxPrep& bp, int64_t n, int32_t bins, float r_max, float sigma, bool adjoint,
                 SmoothPlan* P)
@@ -933,8 +952,8 @@ int smooth_plan(const BoxPrep& bp, int64_t n, int32_t bins, float r_max, float s
     int rc;
     if ((rc = check_cutoff(bp, P->r_s))) return rc;
     make_grid(bp, P->r_s, n, &P->g);
-    const double nodes = ceil(P->r_s / ((double)sigma / 16.0)) + 2.0;
-    P->nodes = adjoint && nodes <= kSmoothMaxNodes ? (int)nodes : 0;
+    P->adjoint = adjoint;
+    P->nodes = adjoint ? smooth_nodes(bp, n, bins, r_max, sigma, P->r_s) : 0;
     P->blocks = smooth_workgroups(adjoint, bp.dim, bins, P->nodes > 0);
     return PPA_OK;
 }
@@ -946,6 +965,7 @@ size_t smooth_layout(const SmoothPlan& P, int64_t n, int32_t bins, void* base_v,
     size_t off = workspace_layout(P.g, n, 0, 0, base_v, W);
     *table = base ? (float4*)(base + off) : nullptr;
     off = (off + sizeof(float4) * (size_t)P.nodes + 255) & ~(size_t)255;
+    if (P.adjoint) return off;  // it has no partial histograms
     *partial = base ? (double*)(base + off) : nullptr;
     off = (off + sizeof(double) * (size_t)P.blocks * (size_t)bins + 255) & ~(size_t)255;
     *level2 = base ? (double*)(base + off) : nullptr;
@@ -1013,8 +1033,9 @@ int run_smooth(const ppa_box* box, const float* pts, int64_t n, int32_t bins, fl
     A.gscale = (float)(A.dr / (sg * sg * sg * sqrt(2.0 * M_PI)));
     A.table = table;
     A.nodes = P.nodes;
-    A.node_w = sg / 16.0;
-    A.inv_node_w = 16.0 / sg;
+    A.node_lanes = smooth_lanes(smooth_terms(bins, r_max, sg));
+    A.node_w = sg / kSmoothNodes;
+    A.inv_node_w = kSmoothNodes / sg;
     A.tscale = -2.0 * A.dr / (sg * sg * sqrt(2.0 * M_PI));
     A.partial = partial;
     A.level2 = level2;

@@ -427,7 +427,15 @@ void launch_knn_list(const KnnListArgs& a, int blocks, hipStream_t s);
 
 // Gaussian-smoothed RDF and its adjoint (smooth.hip).
 constexpr int kSmoothMaxBins = 4096;
-constexpr int kSmoothMaxNodes = 65536;  // of the adjoint's table (1 MiB)
+constexpr int kSmoothMaxNodes = 262144; // of the adjoint's table (4 MiB)
+constexpr double kSmoothNodes = 64.0;   // table nodes per sigma
+
+// Bins in a pair's window, about, and lanes that sum a node of the table.
+inline double smooth_terms(int bins, double r_max, double sigma)
+{
+    return fmin((double)bins, 16.0 * sigma * bins / r_max + 1.0);
+}
+inline int smooth_lanes(double terms) { return terms <= 8.0 ? 4 : 16; }
 
 struct SmoothArgs {
     const float4* cand;       // points sorted by cell (they are also the queries)
@@ -449,6 +457,7 @@ struct SmoothArgs {
     const double* grad_h;     // adjoint: dL/dh [bins]
     float4* table;            // adjoint: [nodes] Taylor coefficients of -2 A at r = i node_w
     int nodes;                // 0: window terms instead of the table
+    int node_lanes;           // 4 or 16
     double node_w, inv_node_w;
     double tscale;            // -2 dr / (sigma^2 sqrt(2 pi)): table weight of the window sums
     float* grad;              // adjoint: dL/dp [n][3], written

@@ -23,7 +23,7 @@
 // gathers each query's row in float64, so every particle's gradient is
 // written once, by the wavefront that owns it, with no atomics.  For given
 // G, A(r) is one smooth function of r for every pair: a small kernel tabulates
-// it with three derivatives at nodes sigma / 16 apart (Hermite functions of
+// it with three derivatives at nodes sigma / 64 apart (Hermite functions of
 // the window terms, summed in float64), and a pair takes one 16-byte read and
 // a cubic instead of its window's terms.  The adjoint recomputes the pairs
 // instead of reading anything stored by the forward.
@@ -171,21 +171,27 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Nodes of the table of -2 A(r): node i at r = i w, w = sigma / 16.  Row i
-// holds the Taylor coefficients in (r - i w) / sigma up to the third: the
-// remainder over half a node, (1/32)^4 / 24 times the fifth Hermite function
-// (at most about 6), is 2.4e-7 of a window term, against the few 1e-6 that
-// float32 window terms by recurrence were off.  16 lanes per node.
+// Nodes of the table of -2 A(r): node i at r = i w, w = sigma / 64.  Row i
+// holds the Taylor coefficients in (r - i w) / sigma up to the third, summed
+// over the bins whose windows reach any pair the node serves (half a node further
+// than 8 sigma).  Relative to a window term at t sigma the remainder over half a node is
+// (1/128)^4 / 24 times the fifth Hermite function over t: 1.5e-7 at 6 sigma, 5e-7 at 8;
+// float32 window terms by recurrence are 1e-6 (bins of 4 sigma) to 6e-3 (sigma / 40)
+// off there.  At sigma / 16 it is 9e-5 and 1.6e-4; the kernel takes as long
+// (131,072 points: 239 us whole call, 241 now).  LANES lanes per node: 4 for few terms, where
+// the sums over the lanes are most of the work.
+template <int LANES>
 __global__ void __launch_bounds__(256) smooth_table_kernel(const SmoothArgs a)
 {
-    const int node = (int)(blockIdx.x * 256 + threadIdx.x) >> 4;
-    const int l = threadIdx.x & 15;
+    const int node = (int)(blockIdx.x * 256 + threadIdx.x) / LANES;
+    const int l = threadIdx.x % LANES;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     const double r = (double)node * a.node_w, inv_s = 8.0 / a.w8;
+    const double reach = a.w8 + 0.5 * a.node_w;
     if (node < a.nodes) {
-        const int b0 = max(0, (int)ceil((r - a.w8) / a.dr - 0.5));
-        const int b1 = min(a.bins - 1, (int)floor((r + a.w8) / a.dr - 0.5));
-        for (int b = b0 + l; b <= b1; b += 16) {
+        const int b0 = max(0, (int)ceil((r - reach) / a.dr - 0.5));
+        const int b1 = min(a.bins - 1, (int)floor((r + reach) / a.dr - 0.5));
+        for (int b = b0 + l; b <= b1; b += LANES) {
             const double t = fma((double)b + 0.5, a.dr, -r) * inv_s, t2 = t * t;
             const double e = a.grad_h[b] * exp(-0.5 * t2);
             s0 = fma(e, t, s0);
@@ -195,7 +201,7 @@ __global__ void __launch_bounds__(256) smooth_table_kernel(const SmoothArgs a)
         }
     }
 #pragma unroll
-    for (int d = 8; d > 0; d >>= 1) {
+    for (int d = LANES / 2; d > 0; d >>= 1) {
         s0 += __shfl_xor(s0, d);
         s1 += __shfl_xor(s1, d);
         s2 += __shfl_xor(s2, d);
@@ -410,7 +416,12 @@ void launch_smooth_fwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s)
 void launch_smooth_bwd(const SmoothArgs& a, int dim, int blocks, hipStream_t s)
 {
     if (a.nodes > 0) {
-        hipLaunchKernelGGL(smooth_table_kernel, dim3((a.nodes + 15) / 16), dim3(256), 0, s, a);
+        const int per = 256 / a.node_lanes;
+        const dim3 grid((a.nodes + per - 1) / per);
+        if (a.node_lanes == 4)
+            hipLaunchKernelGGL(smooth_table_kernel<4>, grid, dim3(256), 0, s, a);
+        else
+            hipLaunchKernelGGL(smooth_table_kernel<16>, grid, dim3(256), 0, s, a);
         if (dim == 3)
             hipLaunchKernelGGL((smooth_kernel<3, true, true>), dim3(blocks), dim3(kBlock), 0, s, a);
         else

@@ -279,3 +279,57 @@ def test_forward_tails(ppa, bins):
     tol = 2.0 ** -24 * (6.0 + 32.0 * t + 1.5 * t * t)
     assert inside.sum() > 8 and np.all(np.abs(h - ref)[inside] <= (tol * ref)[inside])
     assert np.all(h[t > 8.0 + 1e-5] == 0.0)
+
+
+@pytest.mark.parametrize("bins", [8, 64, 1280])
+def test_adjoint_tails(ppa, bins):
+    """The gradient of one bin's weight with respect to a pair, out to 8 sigma, relative
+    to itself: pairs on the nodes of the adjoint's table, between them and anywhere."""
+    r_max, sg = 4.0, 0.125
+    dr = r_max / bins
+    k = np.arange(27)
+    r = 1.75 + k / 512.0 + (k % 3) / 1024.0
+    box, pts = _lone_pairs(r)
+    seen = 0
+    for b in range(0, bins, max(1, bins // 160)):
+        t = ((b + 0.5) * dr - r) / sg
+        take = (np.abs(t) > 0.5) & (np.abs(t) < 8.0 - 1e-5)
+        if not take.any():
+            continue
+        gh = np.zeros(bins)
+        gh[b] = 1.0
+        g = ppa.smooth_rdf_grad(box, pts, bins, r_max, sg, gh).cpu().numpy().astype(np.float64)
+        ref = 2.0 * dr / (sg * sg * math.sqrt(2 * math.pi)) * t * np.exp(-0.5 * t * t)
+        # a cubic over half a node of sigma / 64: (1/128)^4 / 24 of the fifth Hermite
+        # function; eight float32 roundings
+        he5 = np.abs(t ** 5 - 10 * t ** 3 + 15 * t)
+        tol = 1.1 / 128 ** 4 / 24 * he5 / np.abs(t) + 8 * 2.0 ** -24
+        err = np.abs(np.stack([g[27:, 0], -g[:27, 0]]) / np.where(take, ref, 1.0) - 1.0)
+        assert np.all(err[:, take] <= tol[take]), (b, float((err / tol)[:, take].max()))
+        seen += int(take.sum())
+    assert seen > 27
+
+
+@pytest.mark.parametrize("n,bins,sigma", [
+    (2500, 256, 0.02),     # table, 16 lanes a node
+    (2500, 100, 0.004),    # table, 4 lanes a node
+    (2500, 100, 0.0012),   # window terms: few of them against the table's nodes
+    (40000, 2048, 6.2e-4),  # table of nearly the most nodes
+    (40000, 2048, 6.0e-4),  # window terms: more nodes than that
+])
+def test_adjoint_routes(ppa, n, bins, sigma):
+    """The adjoint's table and its window terms, on both sides of the rule between them,
+    against the oracle on a sample of rows."""
+    r_max = 2.5
+    s = workloads.uniform(n, 0.9, seed=95, tilt=(0.1, 0.2, -0.1))
+    rng = np.random.default_rng(96)
+    gh = rng.normal(size=bins)
+    rows = np.sort(rng.permutation(n)[:300])
+    g_ref = oracle.smooth_rdf_grad(_obox(s), s.points, bins, r_max, sigma, gh, rows=rows)
+    g = ppa.smooth_rdf_grad(_box(s), s.points, bins, r_max, sigma, gh).cpu().numpy()[rows]
+    # a stored coordinate is off by up to 2^-24 of its cell (under 8), a pair's
+    # distance by up to 4 of these, a term by that over sigma (times at most 2)
+    tol = GRAD_TOL + 8 * 2.0 ** -24 * 8.0 / sigma
+    d = g.astype(np.float64) - g_ref
+    assert np.linalg.norm(d) < tol * np.linalg.norm(g_ref)
+    assert np.abs(d).max() < tol * np.abs(g_ref).max()
