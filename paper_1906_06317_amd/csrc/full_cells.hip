@@ -11,9 +11,10 @@
 // the rounding of the tests, r2prune), and what is left is compacted into an
 // LDS stage, from which all the queries take it three register slots at a
 // time; the hits' r^2 are compacted again and binned 64 at a time.  In or out
-// is decided by the expanded test where the host allows it and by r^2 itself
-// elsewhere, and bins come from the difference of coordinates, as in the fill
-// pass.  Bound by vector issue (the tests about half) and, at few wavefronts,
+// is decided as in the fill pass without a list, so that a cell's pairs do not depend
+// on the route: by r^2 itself where the stencil fits that pass's register slots, by
+// the expanded test past them where the host allows it.  Bins come from the
+// difference of coordinates.  Bound by vector issue (the tests about half) and, at few wavefronts,
 // by the latency of the compactions.  50,021 points, r = 6, 231 points a cell,
 // 45 M pairs: 231 us with every query of a cell testing every candidate and
 // binning where it was found, 154 us now.
@@ -173,6 +174,65 @@ __device__ __forceinline__ int gather_part(const PairIn& in, float4* stage, int 
     return taken - first;
 }
 
+// One part of a home cell (as gather_part: octant, share, shares) against the cell's
+// stencil in W.st; returns its queries.
+template <int DIM, int EXCL, bool DOT>
+__device__ __forceinline__ int work_part(const PairIn& in, const PairGeom& G, const float4* s_off,
+                                         FullBins& F, int q0, int q1, int oct, int sub, int step)
+{
+    FullLds& W = F.W;
+    const int lane = F.lane;
+    const float r2max = G.r2max;
+    int all = 0;
+    for (int first = 0;; first += kWave) {
+        QueryChunk Q;
+        Q.n = min(kWave, gather_part<DIM>(in, W.stage, q0, q1, oct, sub, step, first, lane));
+        if (Q.n <= 0) break;
+        all += Q.n;
+        Q.q = W.stage[lane < Q.n ? lane : 0];
+        wave_sync();
+        // bounding box of the queries
+        const float lx = wave_min(Q.q.x), hx = wave_max(Q.q.x);
+        const float ly = wave_min(Q.q.y), hy = wave_max(Q.q.y);
+        const float lz = DIM == 3 ? wave_min(Q.q.z) : 0.f;
+        const float hz = DIM == 3 ? wave_max(Q.q.z) : 0.f;
+        int ns = 0;  // candidates staged
+        for (int j = 0; j < G.nsten; ++j) {
+            const int k0 = uniform(W.st.pre[j]), k1 = uniform(W.st.pre[j + 1]);
+            const float4 o = s_off[j];
+            const int base = uniform(W.st.base[j]);
+            for (int k = k0; k < k1; k += kWave) {
+                float4 v = make_float4(kFar, kFar, kFar, 0.f);
+                if (k + lane < k1) {
+                    v = in.cand[base + k + lane];
+                    v.x += o.x;
+                    v.y += o.y;
+                    v.z = DIM == 3 ? v.z + o.z : 0.f;
+                }
+                const float dx = fmaxf(fmaxf(v.x - hx, lx - v.x), 0.f);
+                const float dy = fmaxf(fmaxf(v.y - hy, ly - v.y), 0.f);
+                const float dz = DIM == 3 ? fmaxf(fmaxf(v.z - hz, lz - v.z), 0.f) : 0.f;
+                const bool keep = dist2<DIM>(dx, dy, dz) < G.r2prune;
+                const unsigned long long m = __ballot(keep);
+                if (keep) W.stage[ns + (int)lane_prefix(m)] = v;
+                ns += __popcll(m);
+                if (ns >= kStage) {
+                    run_stage<DIM, EXCL, DOT>(F, Q, r2max, kStage);
+                    wave_sync();
+                    float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+                    ns -= kStage;
+                    if (lane < ns) w = W.stage[kStage + lane];
+                    wave_sync();
+                    if (lane < ns) W.stage[lane] = w;
+                    wave_sync();
+                }
+            }
+        }
+        if (ns > 0) run_stage<DIM, EXCL, DOT>(F, Q, r2max, ns);
+    }
+    return all;
+}
+
 // EXCL: 0 keep j == i, 1 points query themselves (each finds its own entry, at
 // r = 0, which is taken out of bin 0 at the end), 2 separate query points
 // (drop j == i by index).
@@ -195,7 +255,6 @@ __global__ void __launch_bounds__(kBlock, 6) full_cells_kernel(const PairIn in, 
     __syncthreads();
     FullBins F{W, O, lds_hist ? s_hist : nullptr, lane, 0};
     int selfs = 0;
-    const float r2max = G.r2max;
     constexpr int kKinds = DIM == 3 ? 8 : 4;
     int t0, t1, stride;
     wave_tiles_interleaved<kWavesPerBlock>(G.ncells * G.split, wv, t0, t1, stride);
@@ -203,54 +262,12 @@ __global__ void __launch_bounds__(kBlock, 6) full_cells_kernel(const PairIn in, 
         const int tile = uniform(item / G.split), p = item - tile * G.split;
         const int q0 = in.q_start[tile], q1 = in.q_start[tile + 1];
         if (q0 == q1) continue;
-        stencil<DIM>(in, G, tile, lane, W.st);
-        for (int first = 0;; first += kWave) {
-            QueryChunk Q;
-            Q.n = min(kWave, gather_part<DIM>(in, W.stage, q0, q1, p % kKinds, p / kKinds,
-                                              G.split / kKinds, first, lane));
-            if (Q.n <= 0) break;
-            selfs += Q.n;
-            Q.q = W.stage[lane < Q.n ? lane : 0];
-            wave_sync();
-            // bounding box of the queries
-            const float lx = wave_min(Q.q.x), hx = wave_max(Q.q.x);
-            const float ly = wave_min(Q.q.y), hy = wave_max(Q.q.y);
-            const float lz = DIM == 3 ? wave_min(Q.q.z) : 0.f;
-            const float hz = DIM == 3 ? wave_max(Q.q.z) : 0.f;
-            int ns = 0;  // candidates staged
-            for (int j = 0; j < G.nsten; ++j) {
-                const int k0 = uniform(W.st.pre[j]), k1 = uniform(W.st.pre[j + 1]);
-                const float4 o = s_off[j];
-                const int base = uniform(W.st.base[j]);
-                for (int k = k0; k < k1; k += kWave) {
-                    float4 v = make_float4(kFar, kFar, kFar, 0.f);
-                    if (k + lane < k1) {
-                        v = in.cand[base + k + lane];
-                        v.x += o.x;
-                        v.y += o.y;
-                        v.z = DIM == 3 ? v.z + o.z : 0.f;
-                    }
-                    const float dx = fmaxf(fmaxf(v.x - hx, lx - v.x), 0.f);
-                    const float dy = fmaxf(fmaxf(v.y - hy, ly - v.y), 0.f);
-                    const float dz = DIM == 3 ? fmaxf(fmaxf(v.z - hz, lz - v.z), 0.f) : 0.f;
-                    const bool keep = dist2<DIM>(dx, dy, dz) < G.r2prune;
-                    const unsigned long long m = __ballot(keep);
-                    if (keep) W.stage[ns + (int)lane_prefix(m)] = v;
-                    ns += __popcll(m);
-                    if (ns >= kStage) {
-                        run_stage<DIM, EXCL, DOT>(F, Q, r2max, kStage);
-                        wave_sync();
-                        float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
-                        ns -= kStage;
-                        if (lane < ns) w = W.stage[kStage + lane];
-                        wave_sync();
-                        if (lane < ns) W.stage[lane] = w;
-                        wave_sync();
-                    }
-                }
-            }
-            if (ns > 0) run_stage<DIM, EXCL, DOT>(F, Q, r2max, ns);
-        }
+        const int C = stencil<DIM>(in, G, tile, lane, W.st);
+        const int oct = p % kKinds, sub = p / kKinds, step = G.split / kKinds;
+        if (DOT && C > kFillSlots * kWave)
+            selfs += work_part<DIM, EXCL, true>(in, G, s_off, F, q0, q1, oct, sub, step);
+        else
+            selfs += work_part<DIM, EXCL, false>(in, G, s_off, F, q0, q1, oct, sub, step);
     }
     F.drain(true);
     if (EXCL == 1 && selfs > 0 && O.r_min <= 0.f && lane == 0) {

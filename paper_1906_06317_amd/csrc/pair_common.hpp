@@ -9,6 +9,7 @@ namespace ppa {
 namespace pair {
 
 constexpr float kFar = 1.0e18f;
+constexpr int kFillSlots = 10;  // register slots of the fill pass (it needs more registers)
 constexpr int kChunkSlots = 8;  // slots per chunk of an oversized stencil
 
 __device__ __forceinline__ unsigned lane_prefix(unsigned long long mask)

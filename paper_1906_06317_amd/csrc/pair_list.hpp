@@ -47,7 +47,6 @@ using namespace pair;
 
 constexpr int kHitCap = 320;  // hits buffered per wavefront between flushes
 constexpr int kRows = 64;     // rows buffered per wavefront (in a batch, kBatchRows)
-constexpr int kFillSlots = 10;  // register slots of the fill pass (it needs more registers)
 static_assert(kFillSlots * kWave <= kCandCap, "a whole stencil fits the r^2 buffer");
 constexpr int kMaxBatchLdsBins = 1024;  // per-wavefront histograms of a batch up to this size
 

@@ -560,3 +560,29 @@ def test_histogram_of_full_cells(ppa, dim, n, r_max, tilt, r_min, separate):
     own = 0 if r_min > 0.0 else (int(excl[0]) - int(alone[0]))
     assert own == (0 if r_min > 0.0 or separate else n)
     assert torch.equal(excl[1:], alone[1:])
+
+
+def test_histogram_of_full_cells_is_the_sum_over_its_queries(ppa):
+    """One call over full cells against calls on parts of its queries, too few for that
+    route: the same pairs, bin by bin, also where thousands lie at the cutoff to
+    within rounding (a rotated lattice with neighbours at r_max, whose cells
+    have few candidates, beside a dense fluid)."""
+    import torch
+    rng = np.random.default_rng(977)
+    L, a, r_max = 24.5, 1.5, 3.0
+    rot, _ = np.linalg.qr(rng.normal(size=(3, 3)))
+    g = np.arange(-14, 15) * a
+    lat = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3) @ rot.T
+    lat = lat[(np.abs(lat[:, :2]) < L / 2).all(1) & (lat[:, 2] < -0.1) & (lat[:, 2] > -L / 2 + 0.1)]
+    fluid = rng.uniform(-L / 2, L / 2, size=(18000, 3))
+    fluid[:, 2] = np.abs(fluid[:, 2])
+    pts = torch.as_tensor(np.concatenate([lat, fluid]).astype(np.float32)).cuda()
+    n, cells = pts.shape[0], 8 ** 3
+    assert n >= 32 * cells and n * 27 > 640 * cells  # the full-cell route
+    box = ppa.Box((L, L, L), (0.0, 0.0, 0.0), 3)
+    whole = ppa.rdf_counts(box, pts, 60, r_max, exclude_ii=False)
+    parts = torch.zeros_like(whole)
+    for q in pts.split(n // 3 + 1):
+        assert q.shape[0] < 32 * cells
+        ppa.rdf_counts(box, pts, 60, r_max, query_points=q, exclude_ii=False, counts=parts)
+    assert torch.equal(whole, parts), (whole - parts).tolist()[-3:]
