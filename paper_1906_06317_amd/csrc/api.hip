@@ -265,20 +265,15 @@ int pair_split(long long ncells, long long nq)
     return s < 1 ? 1 : (int)s;
 }
 
-// Parts per home cell when the histogram pass splits cells by octants (by
-// quadrants in 2D), or 0 when it does not: where the stencils are on average
-// past the register slots (10 of 64), so that pruning pays, and every octant
-// holds a few queries.  Octants are shared by several wavefronts while there
-// are fewer than about 8192 (6144 are resident; 216 cells, 231 points each: 3456
-// wavefronts 248 us, 5184 167 us, 6912 154 us) and each keeps four queries.
-int octant_split(const Grid& g, int dim, long long n, long long nq)
+// Whether the histogram alone takes the route for full cells: where the stencils are
+// on average past the register slots (10 of 64), so that pruning pays, every octant (in
+// 2D quadrant) holds a few queries, and the bins fit the LDS (5000 bins, 20,000 points at r
+// = 3.3: 333 us by the fill pass, 375 by that route).
+bool full_cells_pay(const Grid& g, int dim, long long n, long long nq, int bins)
 {
     const int kinds = dim == 3 ? 8 : 4;
-    if (g.ncells <= 0 || n * g.nsten <= 640LL * g.ncells || nq < 4LL * kinds * g.ncells) return 0;
-    long long m = 8192 / ((long long)g.ncells * kinds);
-    const long long by_queries = nq / ((long long)g.ncells * kinds * 4);
-    if (m > by_queries) m = by_queries;
-    return kinds * (m < 1 ? 1 : (m > 16 ? 16 : (int)m));
+    return g.ncells > 0 && n * g.nsten > 640LL * g.ncells && nq >= 4LL * kinds * g.ncells &&
+           bins <= kMaxLdsBins;
 }
 
 }  // namespace ppa
@@ -377,8 +372,7 @@ int run_pairs(const QueryCall& c)
         const double r = (double)c.r_max * (1.0 + 2e-5) + 1e-6 * ext;
         A.geom.r2prune = (float)(r * r);
     }
-    const int parts = c.want_nl ? 0 : octant_split(g, bp.dim, c.n, c.nq);
-    if (parts) A.geom.split = parts;
+    const bool full = !c.want_nl && full_cells_pay(g, bp.dim, c.n, c.nq, c.bins);
     A.offsets = c.offsets;
     A.point_idx = c.point_idx;
     A.dist = c.dist;
@@ -401,8 +395,8 @@ int run_pairs(const QueryCall& c)
                               (unsigned long long*)c.n_pairs_dev, s);
     }
     record(pe.ev[2], s);
-    if (parts)
-        launch_full_cells(A, dim, excl, s);
+    if (full)
+        launch_full_cells(A, dim, excl, c.nq, s);
     else
         launch_fill(A, dim, excl, c.want_nl, c.want_hist, s);
     record(pe.ev[3], s);

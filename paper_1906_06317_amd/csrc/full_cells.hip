@@ -3,7 +3,7 @@
 // cutoff that is large against the points' spacing).
 //
 // One wavefront takes the queries of one octant of a home cell (a quadrant in
-// 2D), or an even share of them.  Points near each other share most of their
+// 2D), or a share of them (PartWalk).  Points near each other share most of their
 // candidates, and candidates past the cutoff from the bounding box of the
 // wavefront's queries can hit none of them: an octant's box and the cutoff
 // cover about 10.5 of the 27 cells' volume, of which a query's ball is 4.2.
@@ -17,7 +17,8 @@
 // difference of coordinates.  Bound by vector issue (the tests about half) and, at few wavefronts,
 // by the latency of the compactions.  50,021 points, r = 6, 231 points a cell,
 // 45 M pairs: 231 us with every query of a cell testing every candidate and
-// binning where it was found, 154 us now.
+// binning where it was found, 154 us now.  With more bins than fit the LDS the global
+// atomics bound either way, and the fill pass is taken.
 #include "pair_common.hpp"
 
 namespace ppa {
@@ -39,27 +40,24 @@ struct FullLds {
 
 struct FullOut {
     unsigned long long* hist;
-    int bins;
+    int bins;  // at most kMaxLdsBins
     float r_min, inv_dr;
 };
 
 struct FullBins {
     FullLds& W;
     const FullOut O;
-    unsigned* hist;  // in LDS, or NULL: straight into O.hist
+    unsigned* hist;  // in LDS
     int lane;
     int nh;          // r^2 waiting
 
     __device__ __forceinline__ void bin(float r)
     {
         const float t = (r - O.r_min) * O.inv_dr;
-        if (t >= 0.f && t < (float)O.bins) {
-            const int b = min((int)t, O.bins - 1);
-            if (hist)
-                atomicAdd(&hist[b], 1u);
-            else
-                atomicAdd(&O.hist[b], 1ull);
-        }
+        // keeps the four roots of drain() from being issued together with the bins (2 to
+        // 6 % of the pass)
+        __builtin_amdgcn_sched_barrier(0);
+        if (t >= 0.f && t < (float)O.bins) atomicAdd(&hist[min((int)t, O.bins - 1)], 1u);
     }
     // Bins whole blocks of 64 (or with `all` everything); the rest moves up.
     __device__ __forceinline__ void drain(bool all)
@@ -233,6 +231,95 @@ __device__ __forceinline__ int work_part(const PairIn& in, const PairGeom& G, co
     return all;
 }
 
+// The parts of the home cells: an octant's queries are dealt to shares.  Where the
+// cells of an XCD hold about the same (squared counts at most 1.25 of their mean's
+// square), every octant has as many shares as make kXcdParts parts (768
+// wavefronts of an XCD are resident; 216 cells, 231 points each: 3456 parts in all 248
+// us, 5184 167, 6912 154).  Elsewhere parts are of about equal work, the queries
+// times the candidates, taken as the square of a cell's count: droplets in a dilute system
+// would keep the few wavefronts that have a part of them long after the others ended
+// (20,000 points, three droplets: 1508 us with as many shares everywhere, 469 now).  A share keeps
+// kPartQueries queries.  Each wavefront counts through its XCD's cells, 64 at a
+// time, and takes every stride-th part.
+constexpr int kXcdParts = 1024;
+constexpr int kPartQueries = 4;
+
+template <int KINDS>
+struct PartWalk {
+    int cell, c1;        // first of the cells in the lanes, end of the XCD's
+    int qb, qn;          // this lane's cell: its first query, its queries,
+    int s, incl;         // shares of an octant, and parts up to and with it
+    int before;          // parts of the cells before the lanes'
+    int k, stride;       // this wavefront's next part
+    int alike;           // shares everywhere, or 0 with
+    float per_square;    // shares per squared count
+    int tile, q0, q1, oct, sub, shares;  // the part
+
+    __device__ __forceinline__ PartWalk(const PairIn& in, const PairGeom& G, int wv, int lane)
+    {
+        const int xcd = blockIdx.x & 7;
+        cell = (int)((long long)xcd * G.ncells / 8);
+        c1 = (int)((long long)(xcd + 1) * G.ncells / 8);
+        k = (int)(blockIdx.x >> 3) * kWavesPerBlock + wv;
+        stride = (int)(gridDim.x >> 3) * kWavesPerBlock;
+        before = 0;
+        fetch(in, lane);
+        float sum = (float)qn, sq = sum * sum;
+#pragma unroll 4
+        for (int c = cell + kWave + lane; c < c1; c += kWave) {
+            const float q = (float)(in.q_start[c + 1] - in.q_start[c]);
+            sum += q;
+            sq = fmaf(q, q, sq);
+        }
+        sum = wave_add(sum);
+        sq = wave_add(sq);
+        const int nc = max(1, c1 - cell);
+        const bool even = sq * (float)nc <= 1.25f * sum * sum;
+        const int room = (int)(sum / (float)(kPartQueries * KINDS * nc));
+        alike = even ? max(1, min(kXcdParts / (KINDS * nc), room)) : 0;
+        per_square = (float)(kXcdParts / KINDS) / fmaxf(sq, 1.f);
+        deal();
+    }
+    __device__ __forceinline__ void fetch(const PairIn& in, int lane)
+    {
+        qb = qn = 0;
+        if (cell + lane < c1) {
+            qb = in.q_start[cell + lane];
+            qn = in.q_start[cell + lane + 1] - qb;
+        }
+    }
+    __device__ __forceinline__ void deal()
+    {
+        const float q = (float)qn;
+        s = alike ? alike : max(1, min((int)(per_square * q * q), qn / (kPartQueries * KINDS)));
+        s = qn > 0 ? s : 0;
+        incl = wave_incl_scan(KINDS * s);
+    }
+    // The next part; false at the end.
+    __device__ __forceinline__ bool next(const PairIn& in, int lane)
+    {
+        for (;;) {
+            if (k - before < lane_of(incl, kWave - 1)) {
+                const int l = __ffsll((long long)__ballot(incl > k - before)) - 1;
+                shares = lane_of(s, l);
+                tile = uniform(cell + l);
+                q0 = lane_of(qb, l);
+                q1 = q0 + lane_of(qn, l);
+                const int part = k - before - (lane_of(incl, l) - KINDS * shares);
+                oct = uniform(part % KINDS);
+                sub = uniform(part / KINDS);
+                k += stride;
+                return true;
+            }
+            before += lane_of(incl, kWave - 1);
+            cell += kWave;
+            if (cell >= c1) return false;
+            fetch(in, lane);
+            deal();
+        }
+    }
+};
+
 // EXCL: 0 keep j == i, 1 points query themselves (each finds its own entry, at
 // r = 0, which is taken out of bin 0 at the end), 2 separate query points
 // (drop j == i by index).
@@ -246,63 +333,52 @@ __global__ void __launch_bounds__(kBlock, 6) full_cells_kernel(const PairIn in, 
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = uniform(threadIdx.x / kWave);
     FullLds& W = s_w[wv];
-    const bool lds_hist = O.bins <= kMaxLdsBins;
     if (threadIdx.x < 27)
         s_off[threadIdx.x] = make_float4(G.off[threadIdx.x][0], G.off[threadIdx.x][1],
                                          G.off[threadIdx.x][2], 0.f);
-    if (lds_hist)
-        for (int b = threadIdx.x; b < O.bins; b += kBlock) s_hist[b] = 0u;
+    for (int b = threadIdx.x; b < O.bins; b += kBlock) s_hist[b] = 0u;
     __syncthreads();
-    FullBins F{W, O, lds_hist ? s_hist : nullptr, lane, 0};
+    FullBins F{W, O, s_hist, lane, 0};
     int selfs = 0;
-    constexpr int kKinds = DIM == 3 ? 8 : 4;
-    int t0, t1, stride;
-    wave_tiles_interleaved<kWavesPerBlock>(G.ncells * G.split, wv, t0, t1, stride);
-    for (int item = t0; item < t1; item += stride) {
-        const int tile = uniform(item / G.split), p = item - tile * G.split;
-        const int q0 = in.q_start[tile], q1 = in.q_start[tile + 1];
-        if (q0 == q1) continue;
-        const int C = stencil<DIM>(in, G, tile, lane, W.st);
-        const int oct = p % kKinds, sub = p / kKinds, step = G.split / kKinds;
+    PartWalk<DIM == 3 ? 8 : 4> P(in, G, wv, lane);
+    while (P.next(in, lane)) {
+        const int C = stencil<DIM>(in, G, P.tile, lane, W.st);
         if (DOT && C > kFillSlots * kWave)
-            selfs += work_part<DIM, EXCL, true>(in, G, s_off, F, q0, q1, oct, sub, step);
+            selfs += work_part<DIM, EXCL, true>(in, G, s_off, F, P.q0, P.q1, P.oct, P.sub, P.shares);
         else
-            selfs += work_part<DIM, EXCL, false>(in, G, s_off, F, q0, q1, oct, sub, step);
+            selfs += work_part<DIM, EXCL, false>(in, G, s_off, F, P.q0, P.q1, P.oct, P.sub, P.shares);
     }
     F.drain(true);
-    if (EXCL == 1 && selfs > 0 && O.r_min <= 0.f && lane == 0) {
-        if (lds_hist)
-            atomicSub(&s_hist[0], (unsigned)selfs);
-        else
-            atomicAdd(&O.hist[0], (unsigned long long)(-(long long)selfs));
-    }
+    if (EXCL == 1 && selfs > 0 && O.r_min <= 0.f && lane == 0)
+        atomicSub(&s_hist[0], (unsigned)selfs);
     __syncthreads();
-    if (lds_hist)
-        for (int b = threadIdx.x; b < O.bins; b += kBlock) {
-            const unsigned v = s_hist[b];
-            if (v) atomicAdd(&O.hist[b], (unsigned long long)v);
-        }
+    for (int b = threadIdx.x; b < O.bins; b += kBlock) {
+        const unsigned v = s_hist[b];
+        if (v) atomicAdd(&O.hist[b], (unsigned long long)v);
+    }
 }
 
 template <int DIM, int EXCL, bool DOT>
-void launch_full_t(const PairIn& in, const PairGeom& g, const FullOut& o, hipStream_t s)
+void launch_full_t(const PairIn& in, const PairGeom& g, const FullOut& o, int64_t nq, hipStream_t s)
 {
-    const size_t lds = o.bins <= kMaxLdsBins ? sizeof(unsigned) * (size_t)o.bins : 0;
+    const size_t lds = sizeof(unsigned) * (size_t)o.bins;
     const auto k = full_cells_kernel<DIM, EXCL, DOT>;
-    const int blocks = resident_blocks(k, lds, (long long)g.ncells * g.split);
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), lds, s, in, g, o);
+    const long long more = nq / kPartQueries;  // parts past one an octant, at most
+    const long long parts = (long long)g.ncells * (DIM == 3 ? 8 : 4) +
+                            (more < 8 * kXcdParts ? more : 8 * kXcdParts);
+    hipLaunchKernelGGL(k, dim3(resident_blocks(k, lds, parts)), dim3(kBlock), lds, s, in, g, o);
 }
 
 }  // namespace
 
-void launch_full_cells(const PairArgs& a, int dim, int excl, hipStream_t s)
+void launch_full_cells(const PairArgs& a, int dim, int excl, int64_t nq, hipStream_t s)
 {
     const PairIn in{a.cand, a.cand_start, a.qsorted, a.q_start};
     const FullOut o{a.hist, a.bins, a.r_min, a.inv_dr};
 #define PPA_FULL(D, E)                                         \
     do {                                                       \
-        if (a.geom.dot) launch_full_t<D, E, true>(in, a.geom, o, s); \
-        else launch_full_t<D, E, false>(in, a.geom, o, s);     \
+        if (a.geom.dot) launch_full_t<D, E, true>(in, a.geom, o, nq, s); \
+        else launch_full_t<D, E, false>(in, a.geom, o, nq, s);     \
     } while (0)
     if (dim == 3) {
         if (excl == 1) PPA_FULL(3, 1); else if (excl == 2) PPA_FULL(3, 2); else PPA_FULL(3, 0);

@@ -162,7 +162,6 @@ void launch_build_cells_batch(const float* pts, CellList& cl, const FrameInfo* f
 bool expanded_test_ok(const BoxPrep& bp, const Grid& g, double r);
 int check_cutoff(const BoxPrep& bp, double r);
 int pair_split(long long ncells, long long nq);
-int octant_split(const Grid& g, int dim, long long n, long long nq);
 
 // Geometry of a pair query (pairs.hip).
 struct PairGeom {
@@ -227,9 +226,8 @@ int device_cus();
 
 void launch_count(const PairArgs& a, int dim, int excl, hipStream_t s);
 void launch_fill(const PairArgs& a, int dim, int excl, bool nl, bool hist, hipStream_t s);
-// The histogram alone over cells past the register slots; geom.split parts a
-// cell (octant_split).
-void launch_full_cells(const PairArgs& a, int dim, int excl, hipStream_t s);
+// The histogram alone over cells past the register slots (bins up to kMaxLdsBins).
+void launch_full_cells(const PairArgs& a, int dim, int excl, int64_t nq, hipStream_t s);
 void launch_fill_2d(const PairArgs& a, int excl, bool nl, bool hist, hipStream_t s);
 void launch_fill_3d(const PairArgs& a, int excl, bool nl, bool hist, hipStream_t s);
 // Orders every complete row of a CSR list by neighbour index (distances follow).

@@ -91,6 +91,21 @@ __device__ __forceinline__ float wave_extreme(float v)
 __device__ __forceinline__ float wave_min(float v) { return wave_extreme<false>(v); }
 __device__ __forceinline__ float wave_max(float v) { return wave_extreme<true>(v); }
 
+// Sum over the wavefront by the same steps (uniform; the same for every wavefront
+// with the same values).
+__device__ __forceinline__ float wave_add(float v)
+{
+    auto step = [](float a, int shifted) { return a + __int_as_float(shifted); };
+    const auto bits = [](float a) { return __float_as_int(a); };
+    v = step(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x111, 0xF, 0xF, true));   // row_shr:1
+    v = step(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x112, 0xF, 0xF, true));   // row_shr:2
+    v = step(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x114, 0xF, 0xF, true));   // row_shr:4
+    v = step(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x118, 0xF, 0xF, true));   // row_shr:8
+    v = step(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x142, 0xA, 0xF, false));  // row_bcast:15
+    v = step(v, __builtin_amdgcn_update_dpp(0, bits(v), 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return lane_off(v, kWave - 1);
+}
+
 // x + x of lane l ^ 16 (one permlane16 swap), and of lane l ^ 32.
 __device__ __forceinline__ int pair_sum16(int x)
 {

@@ -586,3 +586,36 @@ def test_histogram_of_full_cells_is_the_sum_over_its_queries(ppa):
         assert q.shape[0] < 32 * cells
         ppa.rdf_counts(box, pts, 60, r_max, query_points=q, exclude_ii=False, counts=parts)
     assert torch.equal(whole, parts), (whole - parts).tolist()[-3:]
+
+
+@pytest.mark.parametrize("system", ["alike", "droplets", "one droplet", "full quadrants"])
+def test_full_cells_of_uneven_systems(ppa, system):
+    """The parts of full cells where the cells are alike, where a few hold most of
+    the work (many shares of an octant, several cells apart) and where a part has more
+    than 64 queries: one call is the sum over calls on parts of its queries,
+    bin by bin, and its own pairs are the diagonal."""
+    import torch
+    rng = np.random.default_rng(981)
+    dim, per = 3, 32
+    if system == "full quadrants":
+        dim, per, L, r_max, m, n = 2, 16, 32.5, 1.0, 32, 310000
+        pts = rng.uniform(-L / 2, L / 2, size=(n, 3))
+        pts[:, 2] = 0
+    else:
+        L, r_max, m, n = 24.5, 3.0, 8, 20000
+        pts = rng.uniform(-L / 2, L / 2, size=(n, 3))
+        if system != "alike":
+            k = 3 if system == "droplets" else 1
+            at = rng.uniform(-L / 2, L / 2, size=(k, 3))
+            pts[:14000] = at[rng.integers(0, k, 14000)] + rng.normal(0, 1.0, size=(14000, 3))
+    pts = torch.as_tensor(pts.astype(np.float32)).cuda()
+    cells = m ** dim
+    assert n >= per * cells and n * 3 ** dim > 640 * cells  # the full-cell route
+    box = ppa.Box((L, L, L if dim == 3 else 1.0), (0.0, 0.0, 0.0), dim)
+    whole = ppa.rdf_counts(box, pts, 70, r_max, exclude_ii=False)
+    parts = torch.zeros_like(whole)
+    for q in pts.split(per * cells - 1):
+        ppa.rdf_counts(box, pts, 70, r_max, query_points=q, exclude_ii=False, counts=parts)
+    assert torch.equal(whole, parts), (whole - parts).tolist()
+    own = ppa.rdf_counts(box, pts, 70, r_max)
+    assert int(whole[0] - own[0]) == n and torch.equal(whole[1:], own[1:])
