@@ -265,6 +265,19 @@ int pair_split(long long ncells, long long nq)
     return s < 1 ? 1 : (int)s;
 }
 
+// Whether the fill pass draws part of its home cells from queues: for a list, where a
+// cell's work (its queries times its candidates, on average) is long against a draw.
+// Against cells all dealt, 2^20 points, whole call: 324 tests a cell (2D, 3 to 15
+// neighbours) 513, 412 and 420 us instead of 469, 400 and 414; 820 (2D, 30) 496 instead of
+// 510; 972 (3D, 3 to 15) 490, 483, 488 instead of 497, 486, 500; 6600 (FCC, 65) 541
+// instead of 566.  Without a list cells are quicker: 972 tests 265 us instead of 225, FCC 254
+// instead of 255.
+bool draws_pay(const Grid& g, long long n, long long nq, bool want_nl)
+{
+    const double cells = (double)g.ncells;
+    return want_nl && (double)nq * (double)n * g.nsten >= 640.0 * cells * cells;
+}
+
 // Whether the histogram alone takes the route for full cells: where the stencils are
 // on average past the register slots (10 of 64), so that pruning pays, every octant (in
 // 2D quadrant) holds a few queries, and the bins fit the LDS (5000 bins, 20,000 points at r
@@ -362,6 +375,7 @@ int run_pairs(const QueryCall& c)
     A.geom.dot = expanded_test_ok(bp, g, c.r_max) ? 1 : 0;
     A.geom.split = pair_split(g.ncells, c.nq);
     A.geom.queue = W.queue;
+    A.geom.draw = draws_pay(g, c.n, c.nq, c.want_nl) ? 1 : 0;
     // a candidate this far (squared) from the bounding box of some queries cannot
     // hit any: the cutoff, 2e-5 of it for the parity band of the tests (1e-5 of
     // r^2, expanded or not) and 1e-6 of the coordinates' range for the box test

@@ -175,6 +175,7 @@ struct PairGeom {
     int split;           // ball query: wavefronts sharing a home cell's queries (0, 1: one)
     float r2prune;       // full cells: squared distance from some queries' bounding box past
                          // which a candidate can hit none (cutoff and the tests' rounding)
+    int draw;            // fill pass: part of the cells drawn from queues (draws_pay)
     int dealt;           // fill pass: rounds of cells dealt in turn (set by its launch)
     unsigned long long* queue;  // zeroed work-queue counters (fill pass)
 };

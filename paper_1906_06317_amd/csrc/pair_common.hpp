@@ -205,8 +205,8 @@ __device__ __forceinline__ void wave_tiles_interleaved(int ncells, int wv, int& 
 // the fill pass kept 3.7 of its 5 wavefronts per SIMD resident on average.  A
 // draw costs an atomic shared by the XCD's wavefronts (about 12 ns each), made
 // one cell ahead.  Fill pass, 2^20-point FCC: 390 us dealt, 379 with one in
-// 8 drawn, 360 with one in 4, the same with one in 2 (which took a list of
-// 7 neighbours a point, whose cells are quick, 250 -> 300 us).  The count pass
+// 8 drawn, 360 with one in 4, the same with one in 2.  Cells that are quick against the
+// draws are all dealt (draws_pay on the host).  The count pass
 // (8 us a cell) waits longer for its draws than they even out: 103 -> 111 us,
 // so it deals.  Under 8 rounds of cells every one is dealt: there a draw each
 // round would cost more than the unevenness.

@@ -537,6 +537,11 @@ __device__ __forceinline__ void fill_chunked(const PairIn& in, const GeomView& G
             Slots<DIM, kChunkSlots> c;
             c.load(in, G.nsten, S, off, k0, C, lane);
             for (int t = 0; t < Q.n; ++t) {
+                // Without a list this loop's time depends on where the lines of the instruction
+                // cache fall in it, and so on code that has nothing to do with it: dilute
+                // droplets, 50,000 points, 1585 us from 16 bytes past a line, 1617 from
+                // 48, 1664 to 1681 from 0, 28 and 32.
+                if constexpr (!NL) asm volatile(".p2align 6\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0");
                 const Query q = Q.get<DIM>(t, r2max);
                 const long long rbase = NL ? lane_of64(rb_v, t) : 0;
                 int w = lane_of(w_v, t);

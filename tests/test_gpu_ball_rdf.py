@@ -619,3 +619,27 @@ def test_full_cells_of_uneven_systems(ppa, system):
     assert torch.equal(whole, parts), (whole - parts).tolist()
     own = ppa.rdf_counts(box, pts, 70, r_max)
     assert int(whole[0] - own[0]) == n and torch.equal(whole[1:], own[1:])
+
+
+@pytest.mark.parametrize("n,r_max", [(480000, 2.6), (480000, 3.0), (560000, 3.4)])
+def test_drawn_and_dealt_cells_in_2d(ppa, n, r_max):
+    """Lists in 2D on both sides of the rule for drawing home cells (queries times
+    candidates of a cell), with enough cells to draw: the fill pass writes the rows that the
+    count pass, which deals its cells, measured."""
+    import torch
+    s = workloads.uniform(n, 1.0, seed=940, dim=2)
+    box = ppa.Box(s.L, s.tilt, s.dim)
+    pts = torch.as_tensor(s.points).cuda()
+    nl = ppa.query_ball(box, pts, r_max)
+    nl.point_idx.fill_(-1)
+    again = ppa.query_ball(box, pts, r_max)
+    assert torch.equal(nl.offsets, again.offsets)
+    q, d = again.query_point_indices().long(), again.point_idx.long()
+    assert int(d.min()) >= 0 and int((q == d).sum()) == 0
+    key = (q * n + d).sort().values
+    assert int((key[1:] == key[:-1]).sum()) == 0
+    # pairs listed from one side only: those within the parity band of the cutoff
+    assert int((~torch.isin(d * n + q, key)).sum()) <= 8e-5 * again.n_pairs
+    x = pts[d, :2] - pts[q, :2]
+    x -= s.L[0] * torch.round(x / s.L[0])
+    assert bool(((x.norm(dim=1) - again.dist).abs() < 1e-3).all())
