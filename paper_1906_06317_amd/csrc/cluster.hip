@@ -12,7 +12,7 @@
 // alternate with passes that point every node at its root, until a round
 // changes nothing, so the
 // large components form flat; a last lock-free union pass over every bond makes the result
-// exact, most of its unions ending after two one-step finds.  Finds in the union passes halve paths with plain stores; the
+// exact, most bonds ending with two equal labels.  Finds in the union passes halve paths with plain stores; the
 // compress passes only read the forest and write their own entries.  A union finds
 // both roots and links the larger under the smaller with a compare-and-swap
 // on the larger root's parent; a failed swap means that root was linked
@@ -81,12 +81,13 @@ __device__ __forceinline__ int root_halving(int* p, int x)
     }
 }
 
-__device__ void unite(int* p, int a, int b)
+// Joins the trees of a and b; returns their common root.
+__device__ int unite(int* p, int a, int b)
 {
     while (true) {
         a = root_halving(p, a);
         b = root_halving(p, b);
-        if (a == b) return;
+        if (a == b) return a;
         if (a < b) {
             const int t = a;
             a = b;
@@ -94,7 +95,7 @@ __device__ void unite(int* p, int a, int b)
         }
         // a > b: hang root a under b unless a stopped being a root
         const int old = atomicCAS(&p[a], a, b);
-        if (old == a) return;
+        if (old == a) return b;
         a = old;
     }
 }
@@ -231,7 +232,8 @@ __global__ void __launch_bounds__(kClBlock) cl_hook_kernel(const int64_t* __rest
     // a symmetric list: a point already in the sampled largest component
     // leaves its bonds to the other ends (a bond to a point outside is in
     // that point's row; a bond inside joins nothing new)
-    if (giant && labels[i] == *giant) return;
+    int li = parent_cached(labels, i);
+    if (giant && li == *giant) return;
     // bounds were checked (and reported) by the seed pass
     long long e0 = offsets[i], e1 = offsets[i + 1];
     if (e0 < 0 || e1 < e0 || e1 > capacity) return;
@@ -240,10 +242,16 @@ __global__ void __launch_bounds__(kClBlock) cl_hook_kernel(const int64_t* __rest
         e0 += pos;
         e1 = e0 + 1;
     }
+    // Two points with one label are joined already, however stale the labels are: a label is
+    // a point of the same tree.  Without this test every bond reads its root through the
+    // caches, and the roots of the components that the rounds left apart are a few lines
+    // that the whole chip waits for (a ladder of 2^20 points in random order 8174 us, 837
+    // now; uniform 2D points past percolation 3659 and 558).
     for (long long e = e0; e < e1; ++e) {
         const int j = idx[e];
         if (j < 0 || j >= n || j == i) continue;
-        unite(labels, i, j);
+        const int lj = parent_cached(labels, j);
+        if (lj != li) li = unite(labels, li, lj);
     }
 }
 
@@ -407,8 +415,7 @@ void launch_cluster(const ClusterArgs& a, hipStream_t s)
     // marks the largest component, whose points the union pass skips (the
     // sampling of the Afforest method).  2^20-point uniform system, r = 1.2
     // (7.2 bonds a point): 1164 us with rounds of one atomic minimum per
-    // bond, 309 us now; r = 0.95, at percolation: 1294 and 370 us, but four
-    // rounds instead of six leave the union pass 2856 us there.
+    // bond, 305 us now; r = 0.95, at percolation: 1294 and 350 us.
     const int rounds = a.capacity < 3 * (long long)n ? 0 : kClRounds;
     for (int r = 0; r < rounds; ++r) {
         const int* prev = r > 0 ? a.round_flags + (r - 1) : nullptr;

@@ -227,3 +227,45 @@ def test_row_lengths_around_the_read_width(ppa, n, symmetric):
     np.testing.assert_array_equal(cidx.cpu().numpy(), oc)
     np.testing.assert_array_equal(sizes.cpu().numpy(), os_)
     assert k == os_.shape[0]
+
+
+def _both_ways(n, a, b):
+    """Symmetric list of the bonds (a[k], b[k])."""
+    q, j = np.concatenate([a, b]), np.concatenate([b, a])
+    order = np.argsort(q, kind="stable")
+    off = np.concatenate([[0], np.cumsum(np.bincount(q, minlength=n))]).astype(np.int64)
+    return off, j[order].astype(np.int32)
+
+
+@pytest.mark.parametrize("graph", ["ladder", "ladders", "tree", "2d", "3d"])
+@pytest.mark.parametrize("symmetric", [True, False])
+def test_components_the_rounds_leave_apart(ppa, graph, symmetric):
+    """Graphs whose large components the hooking rounds do not finish (long and
+    thin ones with points in random order, random geometric graphs at their
+    percolation threshold): the closing union pass joins the rest."""
+    n = 120000
+    rng = np.random.default_rng(720)
+    if graph in ("2d", "3d"):
+        dim = 2 if graph == "2d" else 3
+        s = workloads.uniform(n, 1.0, seed=721, dim=dim)
+        nl = ppa.query_ball(_box(s), s.points, 1.2 if dim == 2 else 0.87)
+        off, idx = nl.offsets.cpu().numpy(), nl.point_idx.cpu().numpy()
+    else:
+        i = np.arange(n)
+        if graph == "tree":
+            a, b = i[1:], (i[1:] - 1) // 2
+            a, b = np.concatenate([a, i[2:]]), np.concatenate([b, i[2:] - 1])
+        else:
+            a = np.concatenate([i[:-1], i[:-2]])
+            b = np.concatenate([i[1:], i[2:]])
+            if graph == "ladders":  # of 7001 points each
+                keep = a // 7001 == b // 7001
+                a, b = a[keep], b[keep]
+        name = rng.permutation(n)
+        off, idx = _both_ways(n, name[a], name[b])
+    assert graph == "3d" or idx.shape[0] >= 3 * n  # the rounds run (in 3D, below: the union pass alone)
+    labels, cidx, sizes, k = ppa.clusters((off, idx), n, symmetric=symmetric)
+    ol, oc, os_ = oracle.clusters(n, off, idx)
+    np.testing.assert_array_equal(labels.cpu().numpy(), ol)
+    np.testing.assert_array_equal(cidx.cpu().numpy(), oc)
+    np.testing.assert_array_equal(sizes.cpu().numpy(), os_)
