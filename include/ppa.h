@@ -24,9 +24,10 @@
  *   the unique periodic image shorter than r_max.
  * Memory.  Every pointer argument named *_dev or documented as "device" is
  *   device memory owned by the caller; the library allocates nothing on the
- *   device.  The scratch space each call needs is the caller's workspace
- *   `ws` of `ws_bytes` bytes (size from ppa_workspace_bytes, 256-byte
- *   aligned).  Inputs must stay valid until the stream work is done.
+ *   device (of pinned host memory one page, see ppa_sync_status).  The
+ *   scratch space each call needs is the caller's workspace `ws` of
+ *   `ws_bytes` bytes (size from ppa_workspace_bytes, 256-byte aligned).
+ *   Inputs must stay valid until the stream work is done.
  * Streams.  All compute calls are asynchronous on the given hipStream_t and
  *   return after enqueueing.  Errors found on the host are returned at
  *   once; errors found on the device (non-finite input, output capacity)
@@ -629,12 +630,19 @@ int ppa_probe_lds_atomics(int32_t log2_bins, int32_t iters, int32_t blocks, uint
 int ppa_probe_global_atomics(int32_t log2_words, int32_t iters, int32_t blocks,
                              uint32_t* hist_dev, hipStream_t stream);
 
-/* Waits for the stream and returns the device status of the last call that
- * used this workspace (ws NULL: the static scratch of ppa_rdf_static on the
- * current device, PPA_EINVAL if no such call was made there) (PPA_OK, PPA_ECAPACITY, PPA_ENONFINITE, for a
- * k-nearest query PPA_ERANGE, and for ppa_steinhardt / ppa_cluster /
- * ppa_knn_from_nlist PPA_EINVAL when a NeighborList offset or index was out
- * of range, PPA_ERANGE for too many ties in ppa_knn_from_nlist). */
+/* Waits until the stream's work so far is done and returns the device status
+ * of the last call that used this workspace (ws NULL: the static scratch of
+ * ppa_rdf_static on the current device, PPA_EINVAL if no such call was made
+ * there): PPA_OK, PPA_ECAPACITY, PPA_ENONFINITE, for a k-nearest query
+ * PPA_ERANGE, and for ppa_steinhardt / ppa_cluster / ppa_knn_from_nlist
+ * PPA_EINVAL when a NeighborList offset or index was out of range, PPA_ERANGE
+ * for too many ties in ppa_knn_from_nlist.
+ * It launches a one-thread kernel on the stream that stores the status to
+ * pinned host memory, and polls for it for up to a millisecond before it sleeps
+ * on the stream.  The process holds one page of 4 KiB for this from the first call
+ * on, in which each call has a place until it returns.  For the static scratch,
+ * on a stream or workspace that is not of the current device, and beside 64 other such
+ * calls it synchronizes the stream and copies the word. */
 int ppa_sync_status(const void* ws, hipStream_t stream);
 
 /* Message describing the calling thread's last error. */

@@ -1074,8 +1074,8 @@ int run_smooth(const ppa_box* box, const float* pts, int64_t n, int32_t bins, fl
 
 // ---------------------------------------------------------------------------
 // Reading a status word: a one-thread kernel behind the stream's work stores
-// it, then a sequence number, to the calling thread's pinned host buffer, and
-// the thread polls for the number.  Waiting for the stream and then copying
+// it, then a sequence number, to a place in pinned host memory, and the
+// calling thread polls for the number.  Waiting for the stream and then copying
 // four bytes took 24 us of every checked call (the wait's wake-up about 12, the
 // copy the rest) past the stream's last kernel; this takes about 8.
 // ---------------------------------------------------------------------------
@@ -1088,64 +1088,89 @@ __global__ void publish_kernel(const unsigned* __restrict__ status, unsigned* ou
     __hip_atomic_store(&out[1], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// One page of pinned host memory per thread that asked for a status, given
-// back when the thread ends.
-struct StatusPage {
-    unsigned* host = nullptr;
-    unsigned seq = 0;
-    bool tried = false;
+// The places: one page of pinned host memory of the process, 64 bytes each.  A
+// call holds one while it polls and gives it back; with all of them held, or no page,
+// the caller waits for the stream instead.  Nothing belongs to a thread, so a
+// thread's end frees nothing (freeing pinned memory waits for the device).
+class StatusPlaces {
+public:
+    static constexpr int kPlaces = 64;
 
-    unsigned* get()
+    int take()
     {
-        if (!tried) {
-            tried = true;
+        std::lock_guard<std::mutex> hold(mu_);
+        if (!page_) {  // tried again by the next call when it fails
             void* p = nullptr;
-            if (hipHostMalloc(&p, 256, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) {
-                host = (unsigned*)p;
-                host[0] = host[1] = 0u;
-            } else {
+            if (hipHostMalloc(&p, 64 * kPlaces, hipHostMallocPortable | hipHostMallocMapped) !=
+                hipSuccess) {
                 (void)hipGetLastError();
+                return -1;
             }
+            page_ = (unsigned*)p;
+            memset(page_, 0, 64 * kPlaces);
         }
-        return host;
+        if (!free_) return -1;
+        const int k = __builtin_ctzll(free_);
+        free_ &= free_ - 1;
+        return k;
     }
-    ~StatusPage()
+    void give_back(int k)
     {
-        if (host) (void)hipHostFree(host);
+        std::lock_guard<std::mutex> hold(mu_);
+        free_ |= 1ull << k;
     }
+    unsigned* at(int k) { return page_ + 16 * k; }
+    unsigned next(int k) { return seq_[k] = seq_[k] + 1 ? seq_[k] + 1 : 1; }  // the holder's
+
+private:
+    std::mutex mu_;
+    unsigned* page_ = nullptr;
+    unsigned long long free_ = ~0ull;
+    unsigned seq_[kPlaces] = {};
 };
 
-thread_local StatusPage g_status_page;
+StatusPlaces g_status_places;
 
-// The status word once the stream's work so far is done; false (nothing
-// waited for, or the stream reported an error) when the caller has to take
-// the ordinary way: no pinned page, a stream or workspace of another device
-// than the current one, or work longer than the polling limit.
-bool published_status(const unsigned* ws, hipStream_t stream, unsigned* st)
+// The status word once the stream's work so far is done.  False (the stream
+// not waited for) when the caller has to take the ordinary way: a stream under
+// capture or of another device than the current one, a workspace elsewhere, no
+// place, or work longer than the polling limit; then `place` is the one a kernel may still
+// write to (or -1), to be given back after the wait.
+bool published_status(const unsigned* ws, hipStream_t stream, unsigned* st, int* place)
 {
+    *place = -1;
     int dev = -1;
     hipDevice_t on = -1;
     hipPointerAttribute_t attr;
-    if (hipGetDevice(&dev) != hipSuccess || hipStreamGetDevice(stream, &on) != hipSuccess ||
-        (int)on != dev || hipPointerGetAttributes(&attr, ws) != hipSuccess ||
-        attr.device != dev || attr.type != hipMemoryTypeDevice) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess ||
+        capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess ||
+        hipStreamGetDevice(stream, &on) != hipSuccess || (int)on != dev ||
+        hipPointerGetAttributes(&attr, ws) != hipSuccess || attr.device != dev ||
+        attr.type != hipMemoryTypeDevice) {
         (void)hipGetLastError();
         return false;
     }
-    unsigned* page = g_status_page.get();
-    if (!page) return false;
-    if (++g_status_page.seq == 0) ++g_status_page.seq;
-    const unsigned seq = g_status_page.seq;
-    hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(1), 0, stream, ws, page, seq);
+    const int k = g_status_places.take();
+    if (k < 0) return false;
+    unsigned* out = g_status_places.at(k);
+    const unsigned seq = g_status_places.next(k);
+    hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(1), 0, stream, ws, out, seq);
+    *place = k;
     if (hipGetLastError() != hipSuccess) return false;
     // poll for up to about a millisecond, then let the ordinary wait sleep
     const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
-    for (int k = 1;; ++k) {
-        if (__atomic_load_n(&page[1], __ATOMIC_ACQUIRE) == seq) {
-            *st = page[0];
+    for (int n = 1;; ++n) {
+        if (__atomic_load_n(&out[1], __ATOMIC_ACQUIRE) == seq) {
+            *st = out[0];
+            g_status_places.give_back(k);
+            *place = -1;
             return true;
         }
-        if (k % 64 == 0 && std::chrono::steady_clock::now() > until) return false;
+        if (n % 64 == 0 && std::chrono::steady_clock::now() > until) return false;
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+        __builtin_ia32_pause();
+#endif
     }
 }
 
@@ -1646,9 +1671,11 @@ int ppa_sync_status(const void* ws, hipStream_t stream)
         ws = p;
     }
     unsigned st = 0;
-    if (is_static || !published_status((const unsigned*)ws, stream, &st)) {
+    int place = -1;
+    if (is_static || !published_status((const unsigned*)ws, stream, &st, &place)) {
         rc = hip_check(hipStreamSynchronize(stream), "stream synchronize");
-        if (rc) return rc;
+        if (rc) return rc;  // a place that a kernel may yet write to stays taken
+        if (place >= 0) g_status_places.give_back(place);
         rc = hip_check(hipMemcpy(&st, ws, sizeof(st), hipMemcpyDeviceToHost), "read status");
         if (rc) return rc;
     }

@@ -643,3 +643,109 @@ def test_drawn_and_dealt_cells_in_2d(ppa, n, r_max):
     x = pts[d, :2] - pts[q, :2]
     x -= s.L[0] * torch.round(x / s.L[0])
     assert bool(((x.norm(dim=1) - again.dist).abs() < 1e-3).all())
+
+
+def _small_checked_call(ppa, seed, stream, ws):
+    import torch
+    s = workloads.uniform(2000, 1.0, seed=seed)
+    with torch.cuda.stream(stream):
+        pts = torch.as_tensor(s.points).cuda()
+        counts = torch.zeros(16, dtype=torch.int64, device="cuda")
+        ppa.rdf_counts(ppa.Box(s.L, s.tilt, s.dim), pts, 16, 2.0, counts=counts, ws=ws,
+                       stream=stream)
+    return counts
+
+
+def test_status_threads_end_beside_long_work(ppa):
+    """A thread that asked for statuses ends while the device is busy with another
+    stream's work: nothing it leaves behind waits for the device."""
+    import os
+    import threading
+    import time
+    import torch
+    side, busy, ws = torch.cuda.Stream(), torch.cuda.Stream(), ppa.Workspace()
+    want = _small_checked_call(ppa, 995, side, ws)
+    a = torch.randn((8192, 8192), device="cuda", dtype=torch.bfloat16)
+    b = torch.empty_like(a)
+    out = {}
+
+    def work():
+        out["counts"] = _small_checked_call(ppa, 995, side, ws)
+        out["tid"] = threading.get_native_id()
+
+    torch.mm(a, a, out=b)
+    torch.cuda.synchronize()
+    done = torch.cuda.Event()
+    with torch.cuda.stream(busy):
+        for _ in range(400):  # about 0.4 s
+            torch.mm(a, a, out=b)
+        done.record()
+    t = threading.Thread(target=work)
+    t.start()
+    t.join()
+    end = time.monotonic() + 20.0
+    while os.path.exists(f"/proc/self/task/{out['tid']}") and time.monotonic() < end:
+        time.sleep(0.001)
+    assert not os.path.exists(f"/proc/self/task/{out['tid']}")
+    assert not done.query(), "the thread's end waited for the device"
+    torch.cuda.synchronize()
+    assert torch.equal(out["counts"], want)
+
+
+def test_status_behind_work_past_the_polling_limit(ppa):
+    """A status asked for behind several milliseconds of work (the read then waits for
+    the stream), and the next ones of the same thread, behind little."""
+    import time
+    import torch
+    s = workloads.uniform(200000, 1.0, seed=997)
+    box = ppa.Box(s.L, s.tilt, s.dim)
+    pts = torch.as_tensor(s.points).cuda()
+    bad = pts.clone()
+    bad[11, 0] = float("inf")
+    want = ppa.rdf_counts(box, pts, 32, 5.0)
+    torch.cuda.synchronize()
+    st, ws = torch.cuda.Stream(), ppa.Workspace()
+    for inputs, code in ((pts, ppa.PPA_OK), (bad, ppa.PPA_ENONFINITE)):
+        h = torch.zeros(32, dtype=torch.int64, device="cuda")
+        torch.cuda.synchronize()
+        for _ in range(40):
+            ppa.rdf_counts(box, pts, 32, 5.0, counts=h, ws=ws, stream=st, check=False)
+        ppa.rdf_counts(box, inputs, 32, 5.0, counts=torch.zeros_like(h), ws=ws, stream=st,
+                       check=False)
+        t0 = time.perf_counter()
+        rc = ws.status(st)
+        assert time.perf_counter() - t0 > 2e-3  # past the polling limit
+        assert rc == code and torch.equal(h, 40 * want)
+        ppa.rdf_counts(box, pts, 32, 5.0, counts=h, ws=ws, stream=st, check=False)
+        assert ws.status(st) == ppa.PPA_OK and torch.equal(h, 41 * want)
+
+
+def test_status_of_many_threads_at_once(ppa):
+    """More threads than places for published statuses, each with its own answer."""
+    import threading
+    import torch
+    s = workloads.uniform(3000, 1.0, seed=998)
+    box = ppa.Box(s.L, s.tilt, s.dim)
+    good = torch.as_tensor(s.points).cuda()
+    bad = good.clone()
+    bad[5, 2] = float("nan")
+    torch.cuda.synchronize()
+    out, gate = {}, threading.Barrier(80)
+
+    def work(k):
+        ws, h = ppa.Workspace(), torch.zeros(8, dtype=torch.int64, device="cuda")
+        gate.wait()
+        out[k] = []
+        for rep in range(5):
+            ppa.rdf_counts(box, bad if (k + rep) % 3 == 0 else good, 8, 2.0, counts=h, ws=ws,
+                           check=False)
+            out[k].append(ws.status())
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(80)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for k in range(80):
+        assert out[k] == [ppa.PPA_ENONFINITE if (k + rep) % 3 == 0 else ppa.PPA_OK
+                          for rep in range(5)], k
