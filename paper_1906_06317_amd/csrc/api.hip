@@ -415,7 +415,7 @@ int run_pairs(const QueryCall& c)
         launch_fill(A, dim, excl, c.want_nl, c.want_hist, s);
     record(pe.ev[3], s);
     if (c.want_nl && (c.flags & PPA_SORT_ROWS))
-        launch_sort_rows(c.offsets, c.nq, c.point_idx, c.dist, c.capacity, s);
+        launch_sort_query_rows(A, W.qry.cell_of, c.nq, dim, excl, s);
     return hip_check(hipGetLastError(), "kernel launch");
 }
 

@@ -232,8 +232,14 @@ void launch_full_cells(const PairArgs& a, int dim, int excl, int64_t nq, hipStre
 void launch_fill_2d(const PairArgs& a, int excl, bool nl, bool hist, hipStream_t s);
 void launch_fill_3d(const PairArgs& a, int excl, bool nl, bool hist, hipStream_t s);
 // Orders every complete row of a CSR list by neighbour index (distances follow).
+// A row cut off by the capacity stays as the fill pass wrote it.
 void launch_sort_rows(const int64_t* offsets, int64_t nq, int32_t* idx, float* dist,
                       int64_t capacity, hipStream_t s);
+// The same for the rows of one frame's query, over cells whose points may be in any order:
+// a row cut off by the capacity is written again in the unsorted order.
+// home: the cell of each query.
+void launch_sort_query_rows(const PairArgs& a, const int* home, int64_t nq, int dim, int excl,
+                            hipStream_t s);
 
 // k nearest neighbours (knn.hip).
 struct KnnGeom {

@@ -749,3 +749,56 @@ def test_status_of_many_threads_at_once(ppa):
     for k in range(80):
         assert out[k] == [ppa.PPA_ENONFINITE if (k + rep) % 3 == 0 else ppa.PPA_OK
                           for rep in range(5)], k
+
+
+@pytest.mark.parametrize("dim,n,r_max,tilt", [(3, 900, 1.5, 0.2), (3, 20000, 1.8, 0.0), (2, 30000, 3.0, 0.3),
+                                              (3, 8000, 3.4, 0.0)])
+@pytest.mark.parametrize("separate", [False, True])
+def test_sorted_rows_cut_off_by_the_capacity(ppa, dim, n, r_max, tilt, separate):
+    """A list with sorted rows that does not fit: whole rows are sorted, and the
+    row that the capacity cuts holds what the unsorted list holds there, call after
+    call."""
+    import ctypes
+    import torch
+    s = workloads.uniform(n, 1.0, seed=985 + n, dim=dim, tilt=(tilt, 0.0, 0.0))
+    box = ppa.Box(s.L, s.tilt, s.dim)
+    pts = torch.as_tensor(s.points).cuda()
+    q = None
+    if separate:
+        q = pts[torch.arange(0, n, 3, device="cuda")] + 0.01
+        q[:, dim:] = 0
+        q = q.contiguous()
+    whole = ppa.query_ball(box, pts, r_max, query_points=q)
+    nq = whole.offsets.shape[0] - 1
+    off = whole.offsets.cpu().numpy()
+    lengths = np.diff(off)
+    ws, cb = ppa.Workspace(), box.c()
+    wptr, wlen = ws.get(ppa.workspace_bytes(box, n, nq if separate else 0, r_max, ppa.PPA_WS_NLIST))
+
+    def run(cap, flags, with_dist=True):
+        o = torch.zeros(nq + 1, dtype=torch.int64, device="cuda")
+        i = torch.full((cap,), -1, dtype=torch.int32, device="cuda")
+        d = torch.full((cap,), -1.0, device="cuda") if with_dist else None
+        total = torch.zeros(1, dtype=torch.int64, device="cuda")
+        p = lambda t: ctypes.c_void_p(t.data_ptr()) if t is not None else None
+        rc = ppa.lib().ppa_query_ball(ctypes.byref(cb), p(pts), n, p(q), nq, r_max,
+                                      0 if separate else 1, flags, wptr, wlen, p(o), None, p(i),
+                                      p(d), cap, p(total), None)
+        assert rc == ppa.PPA_OK
+        assert ws.status(torch.cuda.default_stream()) == ppa.PPA_ECAPACITY
+        assert torch.equal(o, whole.offsets) and int(total) == whole.n_pairs
+        return i, d
+
+    rng = np.random.default_rng(986)
+    rows = rng.permutation(np.flatnonzero(lengths > 6))[:4]
+    for row in rows:
+        for left in (1, int(lengths[row]) // 2, int(lengths[row]) - 1):
+            cap = int(off[row]) + left
+            plain, pd = run(cap, 0)
+            i, d = run(cap, ppa.PPA_SORT_ROWS)
+            assert torch.equal(i[off[row]:], plain[off[row]:]), (row, left)
+            assert torch.equal(d[off[row]:], pd[off[row]:])
+            assert torch.equal(run(cap, ppa.PPA_SORT_ROWS, False)[0], i)
+            j = max(0, row - 50)
+            for k in range(j, row):
+                assert torch.equal(i[off[k]:off[k + 1]], plain[off[k]:off[k + 1]].sort().values)
