@@ -174,12 +174,19 @@ __global__ void __launch_bounds__(kFewBlock) assign_few_kernel(const float* pts,
 // 4096 points 41.0 -> 39.9 us; rows sorted by index 52.4 -> 35.5 and 55.8 -> 44.4 us.
 // An ordered list compares every point with its cell's: at 4096 points in 125
 // cells it took as long as the five launches (19.6 us), so past kSmallPairs
-// comparisons (points times the mean run) those are taken.
+// comparisons (points times the mean run) those are taken.  Where a
+// crowded cell takes a thread more than kSmallRun of them all the same, the points are
+// sorted by cell and index instead (whole call, four droplets of 1024 points 2788 ->
+// 2743 us; of 250 points 175 us sorted, 170 by up to 200 comparisons).
 constexpr int kSmallPoints = 4096;
 constexpr int64_t kSmallPairs = 1 << 16;
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallPer = kSmallPoints / kSmallBlock;
 constexpr int kSmallCells = 8192;
+constexpr int kSmallRun = 400;
+constexpr int kSmallIdBits = 12;
+static_assert(kSmallPoints == 1 << kSmallIdBits && kSmallCells <= 1 << (31 - kSmallIdBits),
+              "cell and index share a word");
 
 template <bool ORDERED>
 __global__ void __launch_bounds__(kSmallBlock) small_cells_kernel(const float* pts, int n,
@@ -193,10 +200,12 @@ __global__ void __launch_bounds__(kSmallBlock) small_cells_kernel(const float* p
     __shared__ int s_id[ORDERED ? kSmallPoints : 1];    // point at a sorted place (arrival order)
     __shared__ int s_cell[ORDERED ? kSmallPoints : 1];  // its cell
     __shared__ int s_pos[ORDERED ? kSmallPoints : 1];   // final place of a point
+    __shared__ int s_long;                              // some thread compares past kSmallRun
     const int tid = threadIdx.x;
     zero_ranges(z);
     __threadfence();  // the status word is cleared before a point sets it
     for (int c = tid; c <= ncells; c += kSmallBlock) s_start[c] = 0;
+    if (tid == 0) s_long = 0;
     __syncthreads();
     float4 v[kSmallPer];
     int cell[kSmallPer], mine[kSmallPer];
@@ -232,6 +241,7 @@ __global__ void __launch_bounds__(kSmallBlock) small_cells_kernel(const float* p
         s_start[c] = run;
         cell_start[c] = run;
         run += cnt;
+        if (ORDERED && cnt * ((n + kSmallBlock - 1) / kSmallBlock) > kSmallRun) s_long = 1;
     }
     if (tid == 0) {
         s_start[ncells] = n;
@@ -242,6 +252,38 @@ __global__ void __launch_bounds__(kSmallBlock) small_cells_kernel(const float* p
 #pragma unroll
         for (int k = 0; k < kSmallPer; ++k)
             if (tid + k * kSmallBlock < n) out[s_start[cell[k]] + mine[k]] = v[k];
+        return;
+    }
+    if (s_long) {
+        // (cell, index) by a bitonic network, padded to a power of two with words that sort
+        // last (s_id)
+        int size = 2;
+        while (size < n) size <<= 1;
+#pragma unroll
+        for (int k = 0; k < kSmallPer; ++k) {
+            const int i = tid + k * kSmallBlock;
+            if (i < size) s_id[i] = i < n ? (cell[k] << kSmallIdBits) | i : INT_MAX;
+        }
+        for (int merge = 2; merge <= size; merge <<= 1)
+            for (int d = merge >> 1; d > 0; d >>= 1) {
+                __syncthreads();
+                for (int t = tid; t < size / 2; t += kSmallBlock) {
+                    const int a = 2 * t - (t & (d - 1)), b = a + d;
+                    const int x = s_id[a], y = s_id[b];
+                    if ((x > y) == ((a & merge) == 0)) {
+                        s_id[a] = y;
+                        s_id[b] = x;
+                    }
+                }
+            }
+        __syncthreads();
+        for (int p = tid; p < n; p += kSmallBlock) s_pos[s_id[p] & (kSmallPoints - 1)] = p;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSmallPer; ++k) {
+            const int i = tid + k * kSmallBlock;
+            if (i < n) out[s_pos[i]] = v[k];
+        }
         return;
     }
 #pragma unroll

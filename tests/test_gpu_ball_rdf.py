@@ -802,3 +802,40 @@ def test_sorted_rows_cut_off_by_the_capacity(ppa, dim, n, r_max, tilt, separate)
             j = max(0, row - 50)
             for k in range(j, row):
                 assert torch.equal(i[off[k]:off[k + 1]], plain[off[k]:off[k + 1]].sort().values)
+
+
+@pytest.mark.parametrize("n", [97, 128, 1000, 2049, 4096])
+@pytest.mark.parametrize("blobs", [1, 4, 40])
+def test_small_builds_with_crowded_cells(ppa, n, blobs):
+    """Rows of small systems whose points crowd a few cells: those of the general build
+    (points far from all others beside them), each stencil cell's by index, call
+    after call."""
+    import torch
+    rng = np.random.default_rng(988 + n + blobs)
+    L, r_max = 26.0, 1.2
+    at = rng.uniform(-8, 8, size=(blobs, 3))
+    pts = at[rng.integers(0, blobs, n)] + rng.normal(0, 0.2 if blobs == 1 else 0.5, size=(n, 3))
+    far = rng.uniform(-12.9, 12.9, size=(20000, 3))
+    far = far[np.abs(far).max(1) > 10.6][:4097]
+    assert far.shape[0] == 4097  # past the one-workgroup build
+    pts = np.clip(pts, -9.2, 9.2).astype(np.float32)
+    box = ppa.Box((L, L, L), (0.0, 0.0, 0.0), 3)
+
+    def rows(points, m):
+        nl = ppa.query_ball(box, torch.as_tensor(points.astype(np.float32)).cuda(), r_max)
+        return nl.offsets.cpu().numpy()[:m + 1], nl.point_idx.cpu().numpy(), nl.dist.cpu().numpy()
+
+    off, idx, dist = rows(pts, n)
+    # each list is in the stencil order of its own grid, with coordinates rounded in
+    # its cells (at most 13 wide: a distance is off by up to 4 roundings of 6.5)
+    off2, idx2, _ = rows(np.concatenate([pts, far]), n)
+    assert np.array_equal(off, off2)
+    for i in range(0, n, max(1, n // 60)):
+        a, b = slice(off[i], off[i + 1]), slice(off2[i], off2[i + 1])
+        assert np.array_equal(np.sort(idx[a]), np.sort(idx2[b]))
+        d = np.linalg.norm(pts[idx[a]].astype(np.float64) - pts[i].astype(np.float64), axis=1)
+        assert np.all(np.abs(dist[a] - d) <= 5 * 2.0 ** -24 * 6.5)
+        # runs of ascending indices: at most one per stencil cell
+        assert int((np.diff(idx[a]) < 0).sum()) <= 26
+    again = rows(pts, n)
+    assert np.array_equal(idx, again[1]) and np.array_equal(dist, again[2])
