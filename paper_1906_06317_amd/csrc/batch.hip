@@ -172,7 +172,7 @@ void enqueue(const ppa_batch_plan* p, int ci, const float* pts, void* ws, const 
     // scan state matches the carved layout)
     Grid g{};
     g.ncells = max_cells(p);
-    launch_zero(W, g, false, nullptr, 0, s);
+    launch_zero(W, g, false, s);
     const FrameInfo* frames = (const FrameInfo*)(base + T.frames_off);
     const int* cell_base = (const int*)(base + T.cell_base_off);
     const int* point_base = (const int*)(base + p->point_base_off);

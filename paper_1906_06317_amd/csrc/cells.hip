@@ -690,8 +690,7 @@ void launch_scan_i64_total(const int* in, int64_t* out, int64_t n, unsigned long
     launch_scan<int64_t>(in, out, n, flags, ticket, total, s);
 }
 
-static ZeroRanges cleared(Workspace& ws, const Grid& g, bool separate_queries, bool cells,
-                          void* extra, size_t extra_bytes)
+static ZeroRanges cleared(Workspace& ws, const Grid& g, bool separate_queries, bool cells)
 {
     ZeroRanges z{};
     auto add = [&](void* p, size_t bytes) {
@@ -711,15 +710,13 @@ static ZeroRanges cleared(Workspace& ws, const Grid& g, bool separate_queries, b
     }
     if (ws.row_scan_flags)
         add(ws.row_scan_flags, sizeof(unsigned long long) * scan_flag_count(ws.qry.n) + 256);
-    if (extra) add(extra, extra_bytes);
     return z;
 }
 
-void launch_zero(Workspace& ws, const Grid& g, bool separate_queries, void* extra,
-                 size_t extra_bytes, hipStream_t s)
+void launch_zero(Workspace& ws, const Grid& g, bool separate_queries, hipStream_t s)
 {
     hipLaunchKernelGGL(zero_kernel, dim3(256), dim3(256), 0, s,
-                       cleared(ws, g, separate_queries, true, extra, extra_bytes));
+                       cleared(ws, g, separate_queries, true));
 }
 
 // Counting sort of the assigned points into their cells: scan of the cell
@@ -807,10 +804,10 @@ void launch_build_cells(const float* pts, const float* qpts, Workspace& W, const
                        (!ordered || W.pts.n * W.pts.n <= kSmallPairs * g.ncells);
     if (small) {
         build_small(pts, W.pts, ab, g.ncells, ordered, W.status,
-                    cleared(W, g, sep, false, nullptr, 0), s);
+                    cleared(W, g, sep, false), s);
         if (sep) build_small(qpts, W.qry, ab, g.ncells, false, W.status, ZeroRanges{}, s);
     } else {
-        launch_zero(W, g, sep, nullptr, 0, s);
+        launch_zero(W, g, sep, s);
         build_general(pts, W.pts, ab, g.ncells, ordered, W.status, s);
         if (sep) build_general(qpts, W.qry, ab, g.ncells, false, W.status, s);
     }

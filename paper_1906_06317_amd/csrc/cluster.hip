@@ -100,15 +100,12 @@ __device__ int unite(int* p, int a, int b)
     }
 }
 
-// Zeroes `words` 32-bit words at z (status, scan state) and words2 at z2
-// (sizes); with n > 0 also sets labels[i] = i.
-__global__ void __launch_bounds__(kClBlock) cl_init_kernel(int n, int* labels, unsigned* z,
-                                                           long long words, unsigned* z2,
-                                                           long long words2)
+// Zeroes `words` 32-bit words at z (status, scan state) and words2 at z2 (sizes).
+__global__ void __launch_bounds__(kClBlock) cl_init_kernel(unsigned* z, long long words,
+                                                           unsigned* z2, long long words2)
 {
     const long long stride = (long long)gridDim.x * kClBlock;
     const long long t = (long long)blockIdx.x * kClBlock + threadIdx.x;
-    for (long long i = t; i < n; i += stride) labels[i] = (int)i;
     for (long long i = t; i < words; i += stride) z[i] = 0u;
     for (long long i = t; i < words2; i += stride) z2[i] = 0u;
 }
@@ -220,11 +217,10 @@ __global__ void __launch_bounds__(kClBlock) cl_sv_kernel(const int64_t* __restri
         __hip_atomic_store(changed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Unites point i with the neighbour at position `pos` of its row (pos >= 0:
-// one sampling round), or with every neighbour (pos < 0).
+// Unites point i with its neighbours.
 __global__ void __launch_bounds__(kClBlock) cl_hook_kernel(const int64_t* __restrict__ offsets,
                                                            const int32_t* __restrict__ idx, int n,
-                                                           long long capacity, int pos,
+                                                           long long capacity,
                                                            const int* giant, int* labels)
 {
     const int i = blockIdx.x * kClBlock + threadIdx.x;
@@ -237,11 +233,6 @@ __global__ void __launch_bounds__(kClBlock) cl_hook_kernel(const int64_t* __rest
     // bounds were checked (and reported) by the seed pass
     long long e0 = offsets[i], e1 = offsets[i + 1];
     if (e0 < 0 || e1 < e0 || e1 > capacity) return;
-    if (pos >= 0) {
-        if (e0 + pos >= e1) return;
-        e0 += pos;
-        e1 = e0 + 1;
-    }
     // Two points with one label are joined already, however stale the labels are: a label is
     // a point of the same tree.  Without this test every bond reads its root through the
     // caches, and the roots of the components that the rounds left apart are a few lines
@@ -393,11 +384,10 @@ void launch_cluster(const ClusterArgs& a, hipStream_t s)
     const bool ranks = a.cluster_idx || a.sizes || a.n_clusters;
     const long long zwords = (long long)(a.zero_bytes / 4);
     const long long swords = a.sizes ? (long long)n : 0;
-    long long most = n > zwords ? n : zwords;
-    if (swords > most) most = swords;
+    const long long most = zwords > swords ? zwords : swords;
     const int ib = (int)(most < 1 ? 1 : (blocks_for(most) < 4096 ? blocks_for(most) : 4096));
-    hipLaunchKernelGGL(cl_init_kernel, dim3(ib), dim3(kClBlock), 0, s, 0, a.labels, a.zero,
-                       zwords, (unsigned*)a.sizes, swords);
+    hipLaunchKernelGGL(cl_init_kernel, dim3(ib), dim3(kClBlock), 0, s, a.zero, zwords,
+                       (unsigned*)a.sizes, swords);
     if (n == 0) return;
     const int nb = blocks_for(n);
     hipLaunchKernelGGL(cl_seed_kernel, dim3(nb), dim3(kClBlock), 0, s, a.offsets, a.idx, n,
@@ -442,7 +432,7 @@ void launch_cluster(const ClusterArgs& a, hipStream_t s)
                            a.giant);
     }
     hipLaunchKernelGGL(cl_hook_kernel, dim3(nb), dim3(kClBlock), 0, s, a.offsets, a.idx, n,
-                       a.capacity, -1, skip_giant ? a.giant : nullptr, a.labels);
+                       a.capacity, skip_giant ? a.giant : nullptr, a.labels);
     hipLaunchKernelGGL(cl_compress_kernel, dim3(nb), dim3(kClBlock), 0, s, n, a.labels,
                        ranks ? a.is_root : nullptr, nullptr);
     if (!ranks) return;

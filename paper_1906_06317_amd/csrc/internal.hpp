@@ -63,8 +63,10 @@ struct CellList {
     int* cell_of;        // [n]
     int* slot;           // [n] arrival slot inside the cell
     float4* local;       // [n] position relative to its cell centre, w = index bits;
-                         //     after the build: sorted by cell, then by index
-    float4* sorted;      // [n] scratch (arrival order inside each cell)
+                         //     after the build: sorted by cell, and inside a cell by index
+                         //     when the build was asked for it (`ordered`), else in order
+                         //     of arrival
+    float4* sorted;      // [n] scratch (the two arrays may change names in the build)
     int* cell_count;     // [ncells]  (zeroed, then counts)
     int* cell_start;     // [ncells + 1]
     unsigned long long* scan_flags;  // decoupled look-back state
@@ -138,8 +140,7 @@ int set_error(int code, const char* fmt, ...);
 int hip_check(hipError_t e, const char* what);
 
 // Launchers (cells.hip).
-void launch_zero(Workspace& ws, const Grid& g, bool separate_queries, void* extra,
-                 size_t extra_bytes, hipStream_t s);
+void launch_zero(Workspace& ws, const Grid& g, bool separate_queries, hipStream_t s);
 // Clears a call's counters and builds the cell lists of its points and, when
 // they are separate (qpts not NULL), of its query points; the sorted points
 // are in W.pts.local and W.qry.local afterwards.  ordered: each cell's run of

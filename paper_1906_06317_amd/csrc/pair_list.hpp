@@ -5,9 +5,9 @@
 // paper credits with a 2x speed-up).
 //
 // Work decomposition (one wavefront per home cell):
-//   * every wavefront owns a contiguous run of home cells; workgroups are
-//     renumbered so the cells of one XCD are contiguous and its L2 sees the
-//     stencil overlap of neighbouring cells;
+//   * the home cells of an XCD are contiguous, and its wavefronts take them in
+//     turn (lists of long cells: the last quarter from a queue), so the cells
+//     in flight are neighbours and its L2 sees their stencils overlap;
 //   * for a home cell, the 27 (2D: 9) stencil cells are gathered into NS
 //     64-wide slots held in registers, each candidate shifted by its stencil
 //     offset so it is relative to the home cell's centre; the code for each
@@ -33,8 +33,9 @@
 // count pass fixed every row's length, the fill pass tests two queries
 // against the same candidate registers at once and places the second row
 // right after the first before either is found; the two independent chains
-// interleave.  The RDF alone (no list) needs only the fill pass.  Stencils with more candidates
-// than the register slots hold are processed in chunks, writing directly.
+// interleave.  The RDF alone (no list) needs only the fill pass, or over full
+// cells one of its own.  Stencils with more candidates than the register slots
+// hold are processed in chunks, writing directly.
 #pragma once
 
 #include "pair_common.hpp"

@@ -86,7 +86,6 @@ void launch_count(const PairArgs& a, int dim, int excl, hipStream_t s)
 #undef PPA_COUNT
 }
 
-// Workgroups for a batch pass: as many as fit at once (times the cap per CU
 void launch_fill(const PairArgs& a, int dim, int excl, bool nl, bool hist, hipStream_t s)
 {
     if (dim == 3)

@@ -15,9 +15,10 @@
 // histogram is privatised per workgroup in LDS, keeping only the bins a bond
 // shorter than r_max can reach (the paper notes that multi-dimensional
 // histograms outgrow the caches first): at 200 x 200 bins on [-3, 3)^2 with
-// r_max = 3 that is 31,450 bins.  When it lets more workgroups share a CU,
-// two 16-bit counters share an LDS word (63 KB instead of 126 KB there, two
-// 1024-thread workgroups per CU instead of one); a counter that reaches 2^15
+// r_max = 3 that is 31,450 bins, 126 KB of counters beside 24 KB of stencils
+// and tables, one 1024-thread workgroup per CU.  Where 32-bit counters do not
+// fit, or two workgroups share a CU by it (14,297 to 28,592 bins), two 16-bit
+// counters share an LDS word; a counter that reaches 2^15
 // hands 2^15 to the caller's count with one global atomic (the lane whose
 // add took it there), so a counter never wraps.  Each workgroup writes its
 // histogram to its own partial array and a second kernel sums the partials
