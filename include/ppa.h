@@ -428,9 +428,10 @@ int ppa_smooth_rdf_fwd(const ppa_box* box, const float* pts, int64_t n, int32_t 
  * device), writes grad_pts[k] = dL/dp_k (float32 [n x 3] device):
  *     dL/dp_k = sum over j != k of 2 A(r_kj) (p_k - p_j) / r_kj,
  *     A(r) = sum_b grad_h[b] dr (c_b - r) / sigma^2 phi(c_b - r)
- * over the same window; pairs at r = 0 add nothing.  The pairs are found
+ * over the same window (to within sigma / 128 at its ends, where terms are
+ * 1e-14 of the largest); pairs at r = 0 add nothing.  The pairs are found
  * again (nothing is kept from the forward); each row is summed in float64
- * by the one wavefront that owns it. */
+ * by the one wavefront that owns it, A to float32 accuracy. */
 int ppa_smooth_rdf_bwd(const ppa_box* box, const float* pts, int64_t n, int32_t bins, float r_max,
                        float sigma, const double* grad_h, int32_t flags, void* ws,
                        size_t ws_bytes, float* grad_pts, hipStream_t stream);
