@@ -265,23 +265,23 @@ int pair_split(long long ncells, long long nq)
     return s < 1 ? 1 : (int)s;
 }
 
-// Whether the fill pass draws part of its home cells from queues: for a list, where a
-// cell's work (its queries times its candidates, on average) is long against a draw.
-// Against cells all dealt, 2^20 points, whole call: 324 tests a cell (2D, 3 to 15
-// neighbours) 513, 412 and 420 us instead of 469, 400 and 414; 820 (2D, 30) 496 instead of
-// 510; 972 (3D, 3 to 15) 490, 483, 488 instead of 497, 486, 500; 6600 (FCC, 65) 541
-// instead of 566.  Without a list cells are quicker: 972 tests 265 us instead of 225, FCC 254
-// instead of 255.
+// Whether the fill pass draws part of its home cells from queues: for a list,
+// where a cell's work (its queries times its candidates, on average) is long
+// against a draw.  Against cells all dealt, 2^20 points, whole call: 324 tests a
+// cell (2D, 3 to 15 neighbours) 513, 412 and 420 us instead of 469, 400 and 414;
+// 820 (2D, 30) 496 instead of 510; 972 (3D, 3 to 15) 490, 483, 488 instead of
+// 497, 486, 500; 6600 (FCC, 65) 541 instead of 566.  Without a list cells are
+// quicker: 972 tests 265 us instead of 225, FCC 254 instead of 255.
 bool draws_pay(const Grid& g, long long n, long long nq, bool want_nl)
 {
     const double cells = (double)g.ncells;
     return want_nl && (double)nq * (double)n * g.nsten >= 640.0 * cells * cells;
 }
 
-// Whether the histogram alone takes the route for full cells: where the stencils are
-// on average past the register slots (10 of 64), so that pruning pays, every octant (in
-// 2D quadrant) holds a few queries, and the bins fit the LDS (5000 bins, 20,000 points at r
-// = 3.3: 333 us by the fill pass, 375 by that route).
+// Whether the histogram alone takes the route for full cells: where the stencils
+// are on average past the register slots (10 of 64), so that pruning pays, every
+// octant (in 2D quadrant) holds a few queries, and the bins fit the LDS (5000
+// bins, 20,000 points at r = 3.3: 333 us by the fill pass, 375 by that route).
 bool full_cells_pay(const Grid& g, int dim, long long n, long long nq, int bins)
 {
     const int kinds = dim == 3 ? 8 : 4;
@@ -932,11 +932,12 @@ struct SmoothPlan {
 };
 
 // Nodes of the adjoint's table, or 0 where the window terms cost less than the
-// table: a node costs its lanes and terms, about five of the units in which a pair's window
-// costs its terms (below 8192 particles or 32 neighbours the chip is not full and a
-// call takes as long).  Table and window terms, whole call: 1000 particles, 12 terms, 10,112 nodes 63
-// and 69 us; 8000, 1.5 terms, 192,512 nodes 81 and 74; 8000, 23 terms, 96,512 nodes
-// 84 and 95; 131,072, 12 terms, 10,112 nodes 241 and 315.
+// table: a node costs its lanes and terms, about five of the units in which a
+// pair's window costs its terms (below 8192 particles or 32 neighbours the chip
+// is not full and a call takes as long).  Table and window terms, whole call:
+// 1000 particles, 12 terms, 10,112 nodes 63 and 69 us; 8000, 1.5 terms, 192,512
+// nodes 81 and 74; 8000, 23 terms, 96,512 nodes 84 and 95; 131,072, 12 terms,
+// 10,112 nodes 241 and 315.
 int smooth_nodes(const BoxPrep& bp, int64_t n, int32_t bins, double r_max, double sigma, double r_s)
 {
     const double nodes = ceil(r_s * kSmoothNodes / sigma) + 2.0;

@@ -11,9 +11,10 @@
 // among the point's neighbours, by plain stores of which any may win)
 // alternate with passes that point every node at its root, until a round
 // changes nothing, so the
-// large components form flat; a last lock-free union pass over every bond makes the result
-// exact, most bonds ending with two equal labels.  Finds in the union passes halve paths with plain stores; the
-// compress passes only read the forest and write their own entries.  A union finds
+// large components form flat; a last lock-free union pass over every bond makes
+// the result exact, most bonds ending with two equal labels.  Finds in the union
+// passes halve paths with plain stores; the compress passes only read the forest
+// and write their own entries.  A union finds
 // both roots and links the larger under the smaller with a compare-and-swap
 // on the larger root's parent; a failed swap means that root was linked
 // meanwhile, and the union continues from its new parent.  Parents only
@@ -233,11 +234,12 @@ __global__ void __launch_bounds__(kClBlock) cl_hook_kernel(const int64_t* __rest
     // bounds were checked (and reported) by the seed pass
     long long e0 = offsets[i], e1 = offsets[i + 1];
     if (e0 < 0 || e1 < e0 || e1 > capacity) return;
-    // Two points with one label are joined already, however stale the labels are: a label is
-    // a point of the same tree.  Without this test every bond reads its root through the
-    // caches, and the roots of the components that the rounds left apart are a few lines
-    // that the whole chip waits for (a ladder of 2^20 points in random order 8174 us, 837
-    // now; uniform 2D points past percolation 3659 and 558).
+    // Two points with one label are joined already, however stale the labels are:
+    // a label is a point of the same tree.  Without this test every bond reads
+    // its root through the caches, and the roots of the components that the
+    // rounds left apart are a few lines that the whole chip waits for (a ladder
+    // of 2^20 points in random order 8174 us, 837 now; uniform 2D points past
+    // percolation 3659 and 558).
     for (long long e = e0; e < e1; ++e) {
         const int j = idx[e];
         if (j < 0 || j >= n || j == i) continue;

@@ -172,8 +172,8 @@ __device__ __forceinline__ int gather_part(const PairIn& in, float4* stage, int 
     return taken - first;
 }
 
-// One part of a home cell (as gather_part: octant, share, shares) against the cell's
-// stencil in W.st; returns its queries.
+// One part of a home cell (octant, share and shares as in gather_part) against
+// the cell's stencil in W.st; returns its queries.
 template <int DIM, int EXCL, bool DOT>
 __device__ __forceinline__ int work_part(const PairIn& in, const PairGeom& G, const float4* s_off,
                                          FullBins& F, int q0, int q1, int oct, int sub, int step)
@@ -231,16 +231,17 @@ __device__ __forceinline__ int work_part(const PairIn& in, const PairGeom& G, co
     return all;
 }
 
-// The parts of the home cells: an octant's queries are dealt to shares.  Where the
-// cells of an XCD hold about the same (squared counts at most 1.25 of their mean's
-// square), every octant has as many shares as make kXcdParts parts (768
-// wavefronts of an XCD are resident; 216 cells, 231 points each: 3456 parts in all 248
-// us, 5184 167, 6912 154).  Elsewhere parts are of about equal work, the queries
-// times the candidates, taken as the square of a cell's count: droplets in a dilute system
-// would keep the few wavefronts that have a part of them long after the others ended
-// (20,000 points, three droplets: 1508 us with as many shares everywhere, 469 now).  A share keeps
-// kPartQueries queries.  Each wavefront counts through its XCD's cells, 64 at a
-// time, and takes every stride-th part.
+// The parts of the home cells: an octant's queries are dealt to shares.  Where
+// the cells of an XCD hold about the same (squared counts at most 1.25 of their
+// mean's square), every octant has as many shares as make kXcdParts parts (768
+// wavefronts of an XCD are resident; 216 cells, 231 points each: 3456 parts in
+// all 248 us, 5184 167, 6912 154).  Elsewhere parts are of about equal work, the
+// queries times the candidates, taken as the square of a cell's count: droplets
+// in a dilute system would keep the few wavefronts that have a part of them long
+// after the others ended (20,000 points, three droplets: 1508 us with as many
+// shares everywhere, 469 now).  A share keeps kPartQueries queries.  Each
+// wavefront counts through its XCD's cells, 64 at a time, and takes every
+// stride-th part.
 constexpr int kXcdParts = 1024;
 constexpr int kPartQueries = 4;
 
@@ -344,9 +345,11 @@ __global__ void __launch_bounds__(kBlock, 6) full_cells_kernel(const PairIn in, 
     while (P.next(in, lane)) {
         const int C = stencil<DIM>(in, G, P.tile, lane, W.st);
         if (DOT && C > kFillSlots * kWave)
-            selfs += work_part<DIM, EXCL, true>(in, G, s_off, F, P.q0, P.q1, P.oct, P.sub, P.shares);
+            selfs += work_part<DIM, EXCL, true>(in, G, s_off, F, P.q0, P.q1, P.oct, P.sub,
+                                                P.shares);
         else
-            selfs += work_part<DIM, EXCL, false>(in, G, s_off, F, P.q0, P.q1, P.oct, P.sub, P.shares);
+            selfs += work_part<DIM, EXCL, false>(in, G, s_off, F, P.q0, P.q1, P.oct, P.sub,
+                                                 P.shares);
     }
     F.drain(true);
     if (EXCL == 1 && selfs > 0 && O.r_min <= 0.f && lane == 0)

@@ -394,7 +394,8 @@ int smooth_workgroups(bool adjoint, int dim, int bins, bool table)
         return dim == 3 ? occupancy_blocks<3, false, false>(dyn)
                         : occupancy_blocks<2, false, false>(dyn);
     }
-    if (table) return dim == 3 ? occupancy_blocks<3, true, true>(0) : occupancy_blocks<2, true, true>(0);
+    if (table)
+        return dim == 3 ? occupancy_blocks<3, true, true>(0) : occupancy_blocks<2, true, true>(0);
     const size_t dyn = sizeof(float) * (size_t)bins;
     return dim == 3 ? occupancy_blocks<3, true, false>(dyn) : occupancy_blocks<2, true, false>(dyn);
 }

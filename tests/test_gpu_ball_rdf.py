@@ -751,8 +751,8 @@ def test_status_of_many_threads_at_once(ppa):
                           for rep in range(5)], k
 
 
-@pytest.mark.parametrize("dim,n,r_max,tilt", [(3, 900, 1.5, 0.2), (3, 20000, 1.8, 0.0), (2, 30000, 3.0, 0.3),
-                                              (3, 8000, 3.4, 0.0)])
+@pytest.mark.parametrize("dim,n,r_max,tilt", [(3, 900, 1.5, 0.2), (3, 20000, 1.8, 0.0),
+                                              (2, 30000, 3.0, 0.3), (3, 8000, 3.4, 0.0)])
 @pytest.mark.parametrize("separate", [False, True])
 def test_sorted_rows_cut_off_by_the_capacity(ppa, dim, n, r_max, tilt, separate):
     """A list with sorted rows that does not fit: whole rows are sorted, and the
